@@ -14,7 +14,7 @@
 //  * init: resets the per-run counters (a kernel, not a memset, so the
 //    sequence stays capturable).
 //
-// Math: bf16 operands, v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  The
+// Math: bf16 operands, v_mfma_f32_16x16x32_bf16 with fp32 accumulation.  The
 // weight tile is the MFMA A operand (output features on the MFMA M side) and
 // the token tile is the B operand, so every lane ends up holding 4
 // consecutive output features of one token row and stores 8 bytes at a time.
@@ -29,7 +29,7 @@
 namespace moe {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Global-memory view of a pointer that was loaded from memory (the receive-buffer table): the
 // compiler cannot infer its address space and would emit flat accesses.
@@ -51,7 +51,7 @@ constexpr int kBlockBytes = kTileM * kRowBytes;        // 32 KiB: one operand of
 constexpr int kRingBlocks = 5;
 constexpr int kLdsBytes = kRingBlocks * kBlockBytes;   // 160 KiB: the whole LDS of a CU
 constexpr int kRowsPerDma = 64 * 16 / kRowBytes;       // 8 rows per DMA instruction
-constexpr int kDmaPerThread = kTileM / kRowsPerDma / 4;  // 8 per operand block per thread
+constexpr int kDmaPerThread = kTileM / kRowsPerDma / 4;  // 8 per weight block per thread
 // Epilogue staging: the finished tile goes through LDS (free once the pipeline drains) so
 // that global stores are whole 16-byte chunks of contiguous rows.  Rows are padded by 16
 // bytes so the 32 lanes writing one column of 32 rows hit distinct banks.
@@ -68,6 +68,8 @@ static_assert(kTileM * kDownOutStride <= kSharedWords, "down staging overlaps th
 constexpr int kDownRowInfo = kTileM * kDownOutStride;
 static_assert(kDownRowInfo + kTileM * 8 <= kSharedWords, "row info overlaps the shared words");
 static_assert(kTileM * kGuOutStride <= kSharedWords, "gate/up staging overlaps the shared words");
+// Part tile of a tail tile in 16-byte quads: 16x16 blocks, row block major, a quad per lane.
+constexpr int kPartQuads = kTileM * kDownTileN / 4;
 
 // Chunk swizzle of the 128-byte operand rows: chunk c of row r is stored at c ^ ((r / 2) % 8).
 // A fragment read (ds_read_b128) is served 16 lanes at a time; those lanes read one chunk
@@ -93,6 +95,24 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
 }
 
 __device__ __forceinline__ uint64_t ticks() { return wall_clock64(); }
+
+// The thread id behind an empty asm statement: what an item computes from it stays in that item.
+// Otherwise the compiler keeps every height's lane offsets in registers across the item loop, past
+// the count that leaves the consumer's waves room beside a producer wave.
+__device__ __forceinline__ int item_thread() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Calls f(integral_constant<int, 0>) .. f(integral_constant<int, n - 1>).
+template <int n, int i = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (i < n) {
+    f(std::integral_constant<int, i>{});
+    static_for<n, i + 1>(f);
+  }
+}
 
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
@@ -123,9 +143,20 @@ __device__ __forceinline__ uint64_t pack_f32x2(float lo, float hi) {
   return (uint64_t)__float_as_uint(lo) | ((uint64_t)__float_as_uint(hi) << 32);
 }
 
+// One wait state separates the scalar write of M0 from the load that reads it: a matrix
+// instruction where there is one (dma_m0 before it, dma16_at_m0 after), else an s_nop.
+template <int kLdsOff>
+__device__ __forceinline__ void dma_m0(uint32_t lds) {
+  asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds), "n"(kLdsOff) : "memory", "scc");
+}
+__device__ __forceinline__ void dma16_at_m0(const uint8_t* sbase, uint32_t voff) {
+  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase) : "memory");
+}
+template <int kLdsOff>
 __device__ __forceinline__ void dma16(const uint8_t* sbase, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase)
-               : "memory");
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff),
+               "s"(sbase), "n"(kLdsOff)
+               : "memory", "scc");
 }
 
 // Waits until at most n of this wave's global loads are outstanding and all LDS reads have
@@ -143,273 +174,303 @@ __device__ __forceinline__ void wait_vm_and_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Rows of one operand as a DMA source.  Instruction i of a wave fetches the 8 rows starting at
-// g_i = min(g0 + 8i, gmax) from the wave-uniform address base + g_i * stride; each lane adds
-// lane_off[i % 2]: its row (lane / 8) times the stride plus its swizzled 16-byte chunk (the
-// swizzle of rows wave*64 + i*8 + lane/8 depends on i only through i % 2).  H and F are
-// multiples of 64, so an 8-row group lies wholly inside or wholly past the operand's last
-// row, and clamping the group start keeps every read in bounds.
+// One operand of an item as a DMA source.  Instruction i of a wave fetches 8 rows: lane l the 16 bytes
+// at base + off[i], its row's (l / 8) 16-byte chunk that belongs at its slot in LDS.  The scalar base
+// advances by `step` per K step, so a DMA costs two instructions beside the matrix ones: with a
+// scalar address per instruction (six more scalar instructions for each) and the ring's slots taken
+// as block % 5 where they were used, a K step opened with about 45 scalar instructions and no matrix
+// instruction in flight.
+template <int kDma>
 struct DmaRows {
   const uint8_t* base;
-  uint32_t stride;
-  int32_t g0, gmax;
-  uint32_t lane_off[2];
-  uint32_t step;  // bytes from one K step of a row to the next (128 when rows are K-contiguous)
-  __device__ __forceinline__ const uint8_t* rows(int i) const {
-    return base + (uint64_t)(uint32_t)min(g0 + 8 * i, gmax) * stride;
-  }
+  uint32_t step;
+  uint32_t off[kDma];
 };
 
-// Lane offset of row lane/8 with its swizzled chunk, for even (p = 0) or odd (p = 1) DMA
-// instructions: the tile row is wave*64 + i*8 + lane/8, whose swizzle is (4*(i%2) + lane/16) % 8.
-__device__ __forceinline__ uint32_t dma_lane_off(int lane, int p, uint32_t stride) {
-  const uint32_t r = (uint32_t)lane >> 3;
-  return r * stride + (((uint32_t)(lane & 7) ^ ((4u * p + (r >> 1)) & 7u)) << 4);
+// Byte offset from the operand rows' start of lane l's chunk of tile row n = first + l / 8, for rows
+// of `stride` bytes of which row `row` (relative to the base) feeds tile row n: chunk c of a row is
+// stored at c ^ swz(n), so the lane at slot l % 8 fetches chunk (l % 8) ^ swz(n).
+__device__ __forceinline__ uint32_t dma_off(uint32_t n, uint32_t row, uint32_t stride, int lane) {
+  return row * stride + (((uint32_t)(lane & 7) ^ swz(n)) << 4);
 }
 
 // ---------------------------------------------------------------------------
-// One 256x256 output tile: acc[i][j] holds D[n][m] for the wave's 128x128
-// quadrant, n = wn*128 + i*32 + 8*(r/4) + 4*(lane/32) + r%4, m = wm*128 + j*32 + lane%32.
-// DMA instruction i of a wave fills operand-tile rows wave*64 + i*8 .. +7 (w for the weight
-// tile, x for the token tile); with kGatherX the token rows are gathered, xoff[i] being this
-// lane's byte offset from x.base for instruction i.
+// The matrix instruction is v_mfma_f32_16x16x32_bf16.  At these sizes the chip is limited by its
+// power, and the 16x16 form (32-deep, a quarter of the accumulator traffic per product of the
+// 32x32x16 form) draws less: with random operands held in registers and no memory traffic it
+// sustained 2.1 PFLOP/s at 2.05 GHz against 1.85 PFLOP/s at 1.79 GHz.  With the K loop below it took
+// the gate/up launch of 18160 rows (H 4096, F 14336) from 3101 to 2825 us (1.38 to 1.51 PFLOP/s).  Written as assembly with
+// the accumulator tied to one AGPR quad: from the builtin the register allocator moves
+// accumulators between registers inside the loop.  The loop's ends keep the distance that
+// reading a result needs (mfma_drain).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void mfma16(f32x4& d, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+}
+
+// An 8-pass matrix instruction's result may be read by a vector instruction 11 wait states on.  The
+// compiler does not see into the assembly, so the wait is written out, and every accumulator passes
+// through a statement after it: a read of one could otherwise be moved up to its last product.
+template <int kNI, int kNJ>
+__device__ __forceinline__ void mfma_drain(f32x4 (&acc)[kNI][kNJ]) {
+  asm volatile("s_nop 15" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < kNI; ++i)
+#pragma unroll
+    for (int j = 0; j < kNJ; ++j) asm volatile("" : "+a"(acc[i][j]));
+}
+
+// ---------------------------------------------------------------------------
+// One output tile of 256 weight rows x 32*kNJ token rows (kNJ 8, 6, 4: 256, 192 or 128 rows) by
+// 2x2 waves of 128 weight rows x 16*kNJ token rows: acc[i][j] holds D[n][m] for
+// n = wn*128 + i*16 + 4*(lane/16) + r, m = wm*16*kNJ + j*16 + lane%16.
+// DMA instruction i of a wave fills operand-tile rows wave*64 + i*8 .. +7 of the weight tile and
+// wave*8*kNJ + i*8 .. +7 of the token tile.
 //
 // Block b of the ring holds the weights (b even) or tokens (b odd) of K step b/2, in slot
-// b % 5.  Prologue: blocks 0-3 in flight.  K step ks runs four 16-deep MFMA sub-steps; each
-// sub-step's 16 MFMAs issue with the next sub-step's 8 fragment reads threaded between them,
-// and with the DMAs of the blocks whose slots are free: block 2ks+4 during sub-step 0 (its
-// slot held K step ks-1's tokens), block 2ks+5 during sub-step 3, after the barrier that
-// ends every wave's reads of step ks.  That barrier also waits for step ks+1's blocks, with
-// only block 2ks+4 allowed in flight.  The last two K steps are peeled so each wait count
-// is a constant on a straight path.
+// b % 5.  Prologue: blocks 0-3 in flight.  K step ks runs two 32-deep sub-steps, each in two
+// halves: the first half multiplies all eight weight fragments by the first kNJ/2 token fragments,
+// the second half by the others.  One buffer per fragment suffices: the second half's token
+// fragments are read under the first half's MFMAs, and the next sub-step's first token fragments
+// and each weight fragment, as its last MFMA has issued, under the second half's (64 vector
+// registers of operands where two buffers would take 128).  The DMAs go out where slots are free:
+// block 2ks+4 in the step's first half sub-step (its slot held K step ks-1's tokens), block 2ks+5
+// in the last one, after the barrier that ends every wave's reads of step ks.  That barrier also
+// waits for step ks+1's blocks, with only block 2ks+4 allowed in flight.  The last two K steps are
+// peeled so each wait count is a constant on a straight path.
 // ---------------------------------------------------------------------------
-template <bool kGatherX, class Late>
-__device__ __forceinline__ void tile_mma(uint8_t* __restrict__ lds, const DmaRows& w, const DmaRows& x,
-                                         const uint32_t (&xoff)[kDmaPerThread], int K, f32x16 (&acc)[4][4],
-                                         Late&& late) {
-  const int tid = threadIdx.x, lane = tid & 63;
+template <int kNJ, class Late>
+__device__ __forceinline__ void tile_mma(uint8_t* __restrict__ lds, DmaRows<kDmaPerThread>& w, DmaRows<kNJ>& x, int K,
+                                         f32x4 (&acc)[8][kNJ], Late&& late) {
+  static_assert(kNJ == 4 || kNJ == 6 || kNJ == 8, "token fragments per wave");
+  constexpr int kHJ = kNJ / 2;
+  const int tid = item_thread(), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = wave & 1, wm = wave >> 1;
-  const int lr = lane & 31, lk = lane >> 5;
-  const uint32_t lsw = swz(lr);  // rows wn*128 + i*32 + lr share lr's swizzle
-  const uint32_t a_row = (uint32_t)(wn * 128 + lr) * kRowBytes;
-  const uint32_t b_row = (uint32_t)(wm * 128 + lr) * kRowBytes;
-  const uint32_t dma_off = (uint32_t)wave * kDmaPerThread * 1024;
+  const int lr = lane & 15, lk = lane >> 4;
+  const uint32_t lsw = swz(lr);  // rows of fragment bases (multiples of 16) + lr share lr's swizzle
 
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
+    for (int j = 0; j < kNJ; ++j) acc[i][j] = f32x4{};
 
   const int nk = K / kTileK;
-  const uint32_t lds0 = lds_addr(lds) + dma_off;
-  auto slot = [](int blk) { return (uint32_t)(blk % kRingBlocks) * kBlockBytes; };
-  auto dma_w = [&](int ks, int q) {
-    dma16(w.rows(q) + (size_t)ks * w.step, w.lane_off[q & 1], lds0 + slot(2 * ks) + q * 1024);
+  const uint32_t lds_w = lds_addr(lds) + (uint32_t)wave * kDmaPerThread * 1024;
+  const uint32_t lds_x = lds_addr(lds) + (uint32_t)wave * kNJ * 1024;
+  // Ring slots by block: o0, o1 hold K step ks's weights and tokens, o2 and o3 step ks+1's, o4 takes
+  // step ks+2's weights and o0, once read, its tokens.  They rotate by two per step.
+  uint32_t o0 = 0, o1 = kBlockBytes, o2 = 2 * kBlockBytes, o3 = 3 * kBlockBytes, o4 = 4 * kBlockBytes;
+  // Fragments of sub-step kk: the lane reads logical chunk 4kk + lk of its row, stored at chunk
+  // (4kk + lk) ^ lsw = (lk ^ lsw) ^ 4kk: one base per operand and sub-step, the slot added, and the
+  // 16-row block an immediate offset.
+  const uint32_t lane_chunk = (uint32_t)lr * kRowBytes + (((uint32_t)lk ^ lsw) << 4);
+  const uint32_t a_lane = (uint32_t)(wn * 128) * kRowBytes + lane_chunk;
+  const uint32_t b_lane = (uint32_t)(wm * 16 * kNJ) * kRowBytes + lane_chunk;
+  bf16x8 fa[8], fb[kNJ];
+  auto read_a = [&](uint32_t slot, int kk, int i) {
+    fa[i] = *(const bf16x8*)(lds + ((a_lane ^ ((uint32_t)kk << 6)) + slot + i * 16 * kRowBytes));
   };
-  auto dma_x = [&](int ks, int q) {
-    if constexpr (kGatherX)
-      dma16(x.base + (size_t)ks * x.step, xoff[q], lds0 + slot(2 * ks + 1) + q * 1024);
-    else
-      dma16(x.rows(q) + (size_t)ks * x.step, x.lane_off[q & 1], lds0 + slot(2 * ks + 1) + q * 1024);
-  };
-  // Fragment q of sub-step kk of K step ks: q < 4 weight rows, else token rows.  The lane
-  // reads logical chunk 2kk + lk of its row, stored at chunk (2kk + lk) ^ lsw = (lk ^ lsw) ^ 2kk;
-  // slot and row offsets are multiples of 128, so the sub-step enters as an XOR of bits 5-6
-  // of one per-operand base and the 32-row block as an immediate offset.
-  const uint32_t a_lane = a_row + (((uint32_t)lk ^ lsw) << 4);
-  const uint32_t b_lane = b_row + (((uint32_t)lk ^ lsw) << 4);
-  auto read_frag = [&](int ks, int kk, int q, bf16x8& dst) {
-    const uint32_t base = q < 4 ? a_lane + slot(2 * ks) : b_lane + slot(2 * ks + 1);
-    dst = *(const bf16x8*)(lds + ((base ^ ((uint32_t)kk << 5)) + (q & 3) * 32 * kRowBytes));
-  };
-  auto mfma = [&](const bf16x8 (&fa)[4], const bf16x8 (&fb)[4], int q) {
-    acc[q >> 2][q & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[q >> 2], fb[q & 3], acc[q >> 2][q & 3], 0, 0, 0);
+  auto read_b = [&](uint32_t slot, int kk, int j) {
+    fb[j] = *(const bf16x8*)(lds + ((b_lane ^ ((uint32_t)kk << 6)) + slot + j * 16 * kRowBytes));
   };
 
-  // Prologue: K steps 0 and 1 in flight, step 0 visible, its first sub-step read.
-#pragma unroll
-  for (int q = 0; q < kDmaPerThread; ++q) dma_w(0, q);
-#pragma unroll
-  for (int q = 0; q < kDmaPerThread; ++q) dma_x(0, q);
+  // Prologue: K steps 0 and 1 in flight, step 0 visible, its first sub-step read.  w.base and x.base
+  // then point at the next step to fetch.
+  auto fetch = [&](uint32_t sw, uint32_t sx) {
+    static_for<kDmaPerThread>([&](auto q) {
+      dma16<decltype(q)::value * 1024>(w.base, w.off[decltype(q)::value], lds_w + sw);
+    });
+    static_for<kNJ>([&](auto q) { dma16<decltype(q)::value * 1024>(x.base, x.off[decltype(q)::value], lds_x + sx); });
+    w.base += w.step;
+    x.base += x.step;
+  };
+  fetch(o0, o1);
   if (nk > 1) {
-#pragma unroll
-    for (int q = 0; q < kDmaPerThread; ++q) dma_w(1, q);
-#pragma unroll
-    for (int q = 0; q < kDmaPerThread; ++q) dma_x(1, q);
-    wait_vm_and_barrier<2 * kDmaPerThread>();
+    fetch(o2, o3);
+    wait_vm_and_barrier<kDmaPerThread + kNJ>();
   } else {
     wait_vm_and_barrier<0>();
   }
-  bf16x8 a0[4], b0[4], a1[4], b1[4];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) read_frag(0, 0, q, q < 4 ? a0[q] : b0[q - 4]);
+  for (int j = 0; j < kHJ; ++j) read_b(o1, 0, j);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) read_a(o0, 0, i);
 
+  // First half of sub-step kk: reads its other token fragments; with kDma, block 2ks+4's DMAs.
+  auto half0 = [&](int kk, auto dma) {
+    static_for<8 * kHJ>([&](auto p) {
+      constexpr int i = decltype(p)::value / kHJ, j = decltype(p)::value % kHJ;
+      constexpr int js = i & 1 ? kHJ - 1 - j : j;
+      constexpr bool fetch_w = decltype(dma)::value && j == 0;
+      if constexpr (fetch_w) dma_m0<i * 1024>(lds_w + o4);
+      mfma16(acc[i][js], fa[i], fb[js]);
+      if constexpr (fetch_w) dma16_at_m0(w.base, w.off[i]);
+      if constexpr (j == 1 && i < kHJ) read_b(o1, kk, kHJ + i);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // Second half: with kRead, reads what the next sub-step (kk1, slots sa and sb) starts with; with
+  // kDma, block 2ks+5's DMAs.
+  auto half1 = [&](uint32_t sa, uint32_t sb, int kk1, auto rd, auto dma) {
+    static_for<8 * kHJ>([&](auto p) {
+      constexpr int i = decltype(p)::value / kHJ, j = decltype(p)::value % kHJ;
+      constexpr int js = kHJ + (i & 1 ? kHJ - 1 - j : j);
+      constexpr bool fetch_x = decltype(dma)::value && j == kHJ / 2 && i < kNJ;
+      if constexpr (fetch_x) dma_m0<i * 1024>(lds_x + o0);
+      mfma16(acc[i][js], fa[i], fb[js]);
+      if constexpr (fetch_x) dma16_at_m0(x.base, x.off[i]);
+      if constexpr (decltype(rd)::value) {
+        if constexpr (j == 0 && i < kHJ) read_b(sb, kk1, i);
+        if constexpr (j == kHJ - 1) read_a(sa, kk1, i);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
   // kind 0: steady step (DMAs, then wait with one block in flight); 1: next to last (no
   // DMAs, wait for everything); 2: last step (no wait, nothing to read ahead).
-  auto step = [&](int ks, auto kind) {
+  auto step = [&](auto kind) {
     constexpr int kd = decltype(kind)::value;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      mfma(a0, b0, q);
-      if (q & 1)
-        read_frag(ks, 1, q >> 1, (q >> 1) < 4 ? a1[q >> 1] : b1[(q >> 1) - 4]);
-      else if constexpr (kd == 0)
-        dma_w(ks + 2, q >> 1);
-      __builtin_amdgcn_sched_barrier(0);
+    using steady = std::integral_constant<bool, kd == 0>;
+    half0(0, steady{});
+    half1(o0, o1, 1, std::true_type{}, std::false_type{});
+    half0(1, std::false_type{});
+    if constexpr (kd < 2) wait_vm_and_barrier<kd == 0 ? kDmaPerThread : 0>();  // step ks+1 visible, step ks's slots free
+    half1(o2, o3, 0, std::integral_constant<bool, (kd < 2)>{}, steady{});
+    if constexpr (kd == 0) {
+      w.base += w.step;
+      x.base += x.step;
     }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      mfma(a1, b1, q);
-      if (q < 8) read_frag(ks, 2, q, q < 4 ? a0[q] : b0[q - 4]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      mfma(a0, b0, q);
-      if (q < 8) read_frag(ks, 3, q, q < 4 ? a1[q] : b1[q - 4]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if constexpr (kd < 2) {
-      wait_vm_and_barrier<kd == 0 ? kDmaPerThread : 0>();  // step ks+1 visible, step ks's slots free
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        mfma(a1, b1, q);
-        if (q & 1)
-          read_frag(ks + 1, 0, q >> 1, (q >> 1) < 4 ? a0[q >> 1] : b0[(q >> 1) - 4]);
-        else if constexpr (kd == 0)
-          dma_x(ks + 2, q >> 1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        mfma(a1, b1, q);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+    const uint32_t t0 = o0, t1 = o1;
+    o0 = o2, o1 = o3, o2 = o4, o3 = t0, o4 = t1;
   };
   int ks = 0;
-  for (; ks + 2 < nk; ++ks) step(ks, std::integral_constant<int, 0>{});
+  for (; ks + 2 < nk; ++ks) step(std::integral_constant<int, 0>{});
   late();  // two K steps (or one) before the end
-  if (ks + 1 < nk) step(ks++, std::integral_constant<int, 1>{});
-  step(ks, std::integral_constant<int, 2>{});
+  if (ks + 1 < nk) step(std::integral_constant<int, 1>{});
+  step(std::integral_constant<int, 2>{});
+  mfma_drain(acc);
   // All waves are done reading LDS before the epilogue or the next tile reuses it.
   wait_vm_and_barrier<0>();
 }
 
-// One work item; `down` selects a down-projection tile (otherwise a fused gate/up tile).
-// Each kind is its own instantiation so the register allocator sees one straight path.
-// One work item.  kSplit (down tiles only) selects the K-part count at compile time: 1 = whole
-// tiles, 2..4 = that many parts, 0 = the count of the item's tile row.  A kernel holding
-// both epilogues would keep copies of the accumulators live across the branch, and a fixed
+// One work item; `down` selects a down-projection tile (otherwise a fused gate/up tile), kRows the
+// token rows computed.  kSplit (down tiles only) selects the K-part count at
+// compile time: 1 = whole tiles, 2..4 = that many parts, 0 = the count of the item's tile row,
+// kSplitDefer = a part that only stores its sums for the tail kernel.  Each combination is its own
+// instantiation so the register allocator sees one straight path: a kernel holding two
+// epilogues of one product would keep copies of the accumulators live across the branch, and a fixed
 // count lets the reduction issue the loads of several blocks of every part at once.
 //
 // `hook()` runs once the epilogue has staged the tile (not on the paths that return early):
 // thread 0 fetches the next item's descriptor there, and the stores that follow hide part of
 // the load latency.  (Branching there while the accumulators are still live, right after the
 // K loop, made the compiler spill them.)
-template <bool down, int kSplit, class Late, class Hook>
+constexpr int kSplitDefer = -2;
+
+template <bool down, int kSplit, int kRows, class Late, class Hook>
 __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t item, const TileRow& tr,
                                               uint8_t* lds, uint32_t* words, Late&& late, Hook&& hook) {
-  const int tid = threadIdx.x, lane = tid & 63;
+  constexpr int kNI = 8;           // weight fragments per wave
+  constexpr int kNJ = kRows / 32;  // token fragments per wave
+  constexpr int kDmaX = kRows / 32;                     // token DMA instructions per wave
+  const int tid = item_thread(), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave: keeps bases scalar
-  const int wn = wave & 1, wm = wave >> 1;
-  const int lr = lane & 31, lk = lane >> 5;
+  const int lr = lane & 15, lk = lane >> 4;
   const int t = (int)((item >> kItemRowShift) & (uint32_t)(kMaxTileRows - 1));
   const int col = down ? (int)((item >> kDownColShift) & kDownColMask) : (int)(item & kItemColMask);
   const int part = down ? (int)(item & kDownPartMask) : 0;
   const int64_t H = a.H, F = a.F;
   const int e = tr.expert, lrow0 = tr.lrow0;
-  // Operand rows: DMA instruction i of a wave fills tile rows wave*64 + i*8 .. +7.  Tensors
-  // stay below 4 GiB per expert/operand, so per-lane offsets fit in 32 bits and the bases are
-  // wave-uniform (scalar registers).
-  DmaRows w, x;
-  uint32_t xoff[kDmaPerThread];
-  if constexpr (!down) {
-    // Waves 0 and 2 fetch gate rows (W1), waves 1 and 3 the matching up rows (W3): tile rows
+  // Where accumulator quad (i, j) lies in the tile: its first weight row and its token row.
+  auto quad_n = [&](int i) { return (wave & 1) * 128 + i * 16 + 4 * lk; };
+  auto quad_m = [&](int j) { return (wave >> 1) * (kRows / 2) + j * 16 + lr; };
+  // Operand rows: DMA instruction i of a wave fills weight-tile rows wave*64 + i*8 .. +7 and
+  // token-tile rows (wave*kDmaX + i)*8 .. +7.  The bases are wave-uniform (scalar registers) and the
+  // offsets from them below 2^32: at most 256 rows of at most 2^17 bytes, or gathered token rows of
+  // a tensor below 4 GiB.
+  DmaRows<kDmaPerThread> w;
+  DmaRows<kDmaX> x;
+  const uint32_t r8 = (uint32_t)lane >> 3;
+  {
+    const uint32_t stride = (uint32_t)(down ? F : H) * 2;
+    // Gate/up: waves 0 and 2 fetch gate rows (W1), waves 1 and 3 the matching up rows (W3): tile rows
     // 0..63 / 128..191 are gate features, 64..127 / 192..255 the same features' up rows, so
-    // each wave's MFMA quadrant holds gate and up of the same 64 features.
-    const uint32_t stride = (uint32_t)H * 2;
-    w.base = (const uint8_t*)((wave & 1) ? a.w3 : a.w1) + (uint64_t)e * F * H * 2;
-    w.stride = stride;
-    w.g0 = col * kGuTileF + (wave >> 1) * 64;
-    w.gmax = (int)F - kRowsPerDma;
-    w.lane_off[0] = dma_lane_off(lane, 0, stride);
-    w.lane_off[1] = dma_lane_off(lane, 1, stride);
+    // each wave's accumulators hold gate and up of the same features.
+    const uint16_t* mat = down ? a.w2 : (wave & 1) ? a.w3 : a.w1;
+    const int n_rows = (int)(down ? H : F);
+    const int g0 = down ? col * kDownTileN + wave * 64 : col * kGuTileF + (wave >> 1) * 64;
+    // H and F are multiples of 64, so an 8-row group lies wholly inside or wholly past the operand's
+    // last row, and clamping the group start keeps every read in bounds.
+    const int gmax = n_rows - kRowsPerDma, gb = min(g0, gmax);
+    w.base = (const uint8_t*)mat + ((uint64_t)e * F * H + (uint64_t)gb * (down ? F : H)) * 2;
     w.step = kRowBytes;
-    // Token rows are gathered from the dispatched rows through row_x.
-    x.base = (const uint8_t*)a.x;
-    x.step = kRowBytes;
-    const uint32_t r = (uint32_t)lane >> 3;
 #pragma unroll
-    for (int i = 0; i < kDmaPerThread; ++i) {
-      const uint32_t n = (uint32_t)(wave * kDmaPerThread + i) * kRowsPerDma + r;
-      // 24-bit multiply (rows < 2^24, stride <= 2^17): a 32-bit result, where a full multiply-add
-      // would produce register pairs whose high halves stay allocated.
-      xoff[i] = __umul24((uint32_t)a.row_x[lrow0 + n], stride) + (((uint32_t)(lane & 7) ^ swz(n)) << 4);
+    for (int i = 0; i < kDmaPerThread; ++i)
+      w.off[i] = dma_off((uint32_t)(8 * i) + r8, (uint32_t)(min(g0 + 8 * i, gmax) - gb) + r8, stride, lane);
+    if constexpr (!down) {
+      // Token rows are gathered from the dispatched rows through row_x.
+      x.base = (const uint8_t*)a.x;
+      x.step = kRowBytes;
+#pragma unroll
+      for (int i = 0; i < kDmaX; ++i) {
+        const uint32_t n = (uint32_t)(wave * kDmaX + i) * kRowsPerDma + r8;
+        x.off[i] = dma_off(n, (uint32_t)a.row_x[lrow0 + n], stride, lane);
+      }
+      // The offsets are complete before the first operand DMA.  The compiler counts only its own
+      // loads, not the DMAs: had it waited for each offset just before its token DMA, each of
+      // those waits would also have drained the weight DMAs issued in between, serialising the
+      // prologue into three memory latencies instead of two.
+#pragma unroll
+      for (int i = 0; i < kDmaX; ++i) asm volatile("" ::"v"(x.off[i]));
+    } else {
+      // Token rows are the tile row's own activation rows in the K-blocked workspace: the 256
+      // rows' 64 features of one K step are one contiguous 32 KiB block.
+      x.base = (const uint8_t*)a.hws + (uint64_t)lrow0 * kRowBytes;
+      x.step = (uint32_t)a.hws_rows * kRowBytes;
+#pragma unroll
+      for (int i = 0; i < kDmaX; ++i) {
+        const uint32_t n = (uint32_t)(wave * kDmaX + i) * kRowsPerDma + r8;
+        x.off[i] = dma_off(n, n, kRowBytes, lane);
+      }
     }
-    // The offsets are complete before the first operand DMA.  The compiler counts only its own
-    // loads, not the DMAs: had it waited for each offset just before its token DMA, each of
-    // those waits would also have drained the weight DMAs issued in between, serialising the
-    // prologue into three memory latencies instead of two.
-#pragma unroll
-    for (int i = 0; i < kDmaPerThread; ++i) asm volatile("" ::"v"(xoff[i]));
-  } else {
-    const uint32_t stride = (uint32_t)F * 2;
-    w.base = (const uint8_t*)a.w2 + (uint64_t)e * H * F * 2;
-    w.stride = stride;
-    w.g0 = col * kDownTileN + wave * 64;
-    w.gmax = (int)H - kRowsPerDma;
-    w.lane_off[0] = dma_lane_off(lane, 0, stride);
-    w.lane_off[1] = dma_lane_off(lane, 1, stride);
-    w.step = kRowBytes;
-    // Token rows are the tile row's own activation rows in the K-blocked workspace: the 256
-    // rows' 64 features of one K step are one contiguous 32 KiB block.
-    x.base = (const uint8_t*)a.hws + (uint64_t)lrow0 * kRowBytes;
-    x.stride = kRowBytes;
-    x.g0 = wave * 64;
-    x.gmax = kTileM - kRowsPerDma;
-    x.lane_off[0] = dma_lane_off(lane, 0, kRowBytes);
-    x.lane_off[1] = dma_lane_off(lane, 1, kRowBytes);
-    x.step = (uint32_t)a.hws_rows * kRowBytes;
   }
 
   // K range of this item: all of it, or one of split_k near-equal runs of K steps.
   int kbeg = 0, klen = down ? (int)F : (int)H;
   constexpr bool split = kSplit != 1;
-  const int S = kSplit == 0 ? tr.split : kSplit;
+  const int S = kSplit <= 0 ? tr.split : kSplit;
   if (split) {
     const int nk = (int)F / kTileK;
     const int s0 = part * nk / S, s1 = (part + 1) * nk / S;
     kbeg = s0 * kTileK;
     klen = (s1 - s0) * kTileK;
   }
-  f32x16 acc[4][4];
+  f32x4 acc[kNI][kNJ];
   w.base += (size_t)(kbeg / kTileK) * w.step;
   x.base += (size_t)(kbeg / kTileK) * x.step;
-  tile_mma<!down>(lds, w, x, xoff, klen, acc, late);
+  tile_mma<kNJ>(lds, w, x, klen, acc, late);
 
   if constexpr (!down) {
-    // Gated activation a = bf16(silu(g) * u): lane values -> LDS tile [256 rows][128 features].
+    // Gated activation a = bf16(silu(g) * u): lane values -> LDS tile [kRows rows][128 features].
+    // The up quad of gate quad (i, j) is (i + kNI/2, j), 64 tile rows on.
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = wm * 128 + j * 32 + lr;
+    for (int j = 0; j < kNJ; ++j) {
+      const int m = quad_m(j);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int fl = wn * 64 + i * 32 + 8 * q + 4 * lk;
-          const f32x16& g = acc[i][j];
-          const f32x16& u = acc[i + 2][j];
-          uint2 v;
-          v.x = pack_bf16x2(silu_mul(g[4 * q + 0], u[4 * q + 0]), silu_mul(g[4 * q + 1], u[4 * q + 1]));
-          v.y = pack_bf16x2(silu_mul(g[4 * q + 2], u[4 * q + 2]), silu_mul(g[4 * q + 3], u[4 * q + 3]));
-          *(uint2*)(lds + m * kGuOutStride + fl * 2) = v;
-          // Convert block by block: without this the scheduler hoists every accumulator
-          // read ahead of the LDS writes and runs out of VGPRs.
-          __builtin_amdgcn_sched_barrier(0);
-        }
+      for (int i = 0; i < kNI / 2; ++i) {
+        const int n = quad_n(i);                     // a gate row: 0..63 or 128..191
+        const int fl = (n >> 7) * 64 + (n & 63);
+        const f32x4& g = acc[i][j];
+        const f32x4& u = acc[i + kNI / 2][j];
+        uint2 v;
+        v.x = pack_bf16x2(silu_mul(g[0], u[0]), silu_mul(g[1], u[1]));
+        v.y = pack_bf16x2(silu_mul(g[2], u[2]), silu_mul(g[3], u[3]));
+        *(uint2*)(lds + m * kGuOutStride + fl * 2) = v;
+        // Convert block by block: without this the scheduler hoists every accumulator
+        // read ahead of the LDS writes and runs out of VGPRs.
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     __syncthreads();
     hook();
@@ -423,36 +484,43 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
     // per-row lookup sits between the staged tile and its stores.
     if (f < F) {
 #pragma unroll 4
-      for (int p = 0; p < kTileM / 16; ++p) {
+      for (int p = 0; p < kRows / 16; ++p) {
         const int m = p * 16 + (tid >> 4);
         *(u32x4*)(blk + (size_t)(lrow0 + m) * kTileK) = *(const u32x4*)(lds + m * kGuOutStride + c16 * 16);
       }
     }
+  } else if constexpr (kSplit == kSplitDefer) {
+    // A part of a tail tile: its fp32 sums, one 16x16 block per wave store of 1 KiB, where the tail
+    // kernel (a launch of its own, so ordinary stores reach it) adds the parts.
+    f32x4* mine = (f32x4*)a.partials + ((size_t)tr.part_base + (size_t)col * S + part) * kPartQuads + lane;
+#pragma unroll
+    for (int j = 0; j < kNJ; ++j)
+#pragma unroll
+      for (int i = 0; i < kNI; ++i)
+        mine[(size_t)((quad_m(j) >> 4) * (kDownTileN / 16) + (quad_n(i) >> 4)) * 64] = acc[i][j];
   } else {
     // Split K: every part stores its fp32 accumulators (in register order, so each thread
     // reads back exactly the positions it wrote) and counts itself in; the part that arrives
     // last reads all parts back and adds them in part order -- a fixed order whichever part
     // that is -- and writes the tile.  A part tile is 128 slices of 256 threads x 8 bytes:
-    // slice 2b + h holds half h of accumulator block b = (i*4 + j)*4 + q.
+    // slice 2b + h holds half h of accumulator quad b = i*8 + j.
     const int tile = t * a.down_per_row + col;
     constexpr int kPartU64 = kProducerThreads * 128;  // 8-byte elements per part tile
     const uint64_t* parts = nullptr;
     if constexpr (split) {
+      static_assert(!split || kRows == kTileM, "explicit splits take whole tile rows");
       const size_t first = (size_t)tr.part_base + (size_t)col * S;  // this tile's part 0
       parts = (const uint64_t*)a.partials + first * kPartU64;
       uint64_t* mine = (uint64_t*)a.partials + (first + part) * kPartU64 + tid;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < kNI; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x16& d = acc[i][j];
-            const int b = (i * 4 + j) * 4 + q;
-            store8_device(mine + (2 * b) * kProducerThreads, pack_f32x2(d[4 * q], d[4 * q + 1]));
-            store8_device(mine + (2 * b + 1) * kProducerThreads, pack_f32x2(d[4 * q + 2], d[4 * q + 3]));
-          }
-      if (kSplit == 0 && (a.mode & kModeDeferTail)) return;  // the tail kernel adds the parts
+        for (int j = 0; j < kNJ; ++j) {
+          const f32x4& d = acc[i][j];
+          const int b = i * kNJ + j;
+          store8_device(mine + (2 * b) * kProducerThreads, pack_f32x2(d[0], d[1]));
+          store8_device(mine + (2 * b + 1) * kProducerThreads, pack_f32x2(d[2], d[3]));
+        }
       wait_vm_and_barrier<0>();  // every wave's part stores have reached the coherence point
       if (tid == 0) {
         const uint32_t prev =
@@ -468,16 +536,14 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
     static_assert(kProducerThreads == kTileM, "one row per thread");
     const int my_rank = a.row_rank[lrow0 + tid], my_slot = a.row_slot[lrow0 + tid];
     int32_t* rinfo = (int32_t*)(lds + kDownRowInfo);
-    // Down-projection output: lane values -> LDS tile [256 rows][256 hidden columns].
-    auto stage_out = [&](int i, int j, int q, float4 s) {
-      const int m = wm * 128 + j * 32 + lr;
-      const int nl = wn * 128 + i * 32 + 8 * q + 4 * lk;
+    // Down-projection output: lane values -> LDS tile [kRows rows][256 hidden columns].
+    auto stage_out = [&](int i, int j, float4 s) {
       uint2 v;
       v.x = pack_bf16x2(s.x, s.y);
       v.y = pack_bf16x2(s.z, s.w);
-      *(uint2*)(lds + m * kDownOutStride + nl * 2) = v;
+      *(uint2*)(lds + quad_m(j) * kDownOutStride + quad_n(i) * 2) = v;
     };
-    // Accumulator block b of part p: its two 8-byte halves, widened back to four floats.
+    // Accumulator quad b of part p: its two 8-byte halves, widened back to four floats.
     auto part_block = [&](const uint64_t* src, int p, int b) {
       const uint64_t lo = src[(size_t)p * kPartU64 + (2 * b) * kProducerThreads];
       const uint64_t hi = src[(size_t)p * kPartU64 + (2 * b + 1) * kProducerThreads];
@@ -516,10 +582,7 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
             }
         }
 #pragma unroll
-        for (int u = 0; u < kB; ++u) {
-          const int b = b0 + u;
-          stage_out(b >> 4, (b >> 2) & 3, b & 3, acc4[u]);
-        }
+        for (int u = 0; u < kB; ++u) stage_out((b0 + u) >> 3, (b0 + u) & 7, acc4[u]);
       }
     } else if constexpr (split) {
       // kSplit parts: all parts read back (this part's too: the same values, and no branch
@@ -543,21 +606,18 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
             s.z += v[u][p].z;
             s.w += v[u][p].w;
           }
-          const int b = b0 + u;
-          stage_out(b >> 4, (b >> 2) & 3, b & 3, s);
+          stage_out((b0 + u) >> 3, (b0 + u) & 7, s);
         }
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < kNJ; ++j)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x16& d = acc[i][j];
-            stage_out(i, j, q, float4{d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]});
-            __builtin_amdgcn_sched_barrier(0);  // block by block (see above)
-          }
+        for (int i = 0; i < kNI; ++i) {
+          const f32x4& d = acc[i][j];
+          stage_out(i, j, float4{d[0], d[1], d[2], d[3]});
+          __builtin_amdgcn_sched_barrier(0);  // block by block (see above)
+        }
     }
     rinfo[2 * tid] = my_rank;
     rinfo[2 * tid + 1] = my_slot;
@@ -575,7 +635,7 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
       const int c8 = tid & 63;
       const int n = col * kDownTileN + c8 * 4;
 #pragma unroll 4
-      for (int p = 0; p < kTileM / 4; ++p) {
+      for (int p = 0; p < kRows / 4; ++p) {
         const int m = p * 4 + (tid >> 6);
         const int lrow = lrow0 + m;
         const int rank = rinfo[2 * m];
@@ -594,7 +654,7 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
       const int c16 = tid & 31;
       const int n = col * kDownTileN + c16 * 8;
 #pragma unroll 4
-      for (int p = 0; p < kTileM / 8; ++p) {
+      for (int p = 0; p < kRows / 8; ++p) {
         const int m = p * 8 + (tid >> 5);
         const int lrow = lrow0 + m;
         const int rank = rinfo[2 * m];
@@ -810,14 +870,17 @@ __global__ __launch_bounds__(kProducerThreads, 1) void producer_kernel(ProducerA
     auto hook = [&]() {
       if (tid == 0) next_resolve(a, nx, end);
     };
+    auto run = [&](auto split) {
+      producer_item<down, decltype(split)::value, kTileM>(a, item, tr, lds, words, late, hook);
+    };
     if constexpr (kSplit < 0) {
-      // Split per tile row: whole tiles take the plain epilogue, split rows the part path.
+      // Split per tile row: whole tiles take the plain epilogue, split rows only store their parts.
       if (tr.split == 1)
-        producer_item<down, 1>(a, item, tr, lds, words, late, hook);
+        run(std::integral_constant<int, 1>{});
       else
-        producer_item<down, 0>(a, item, tr, lds, words, late, hook);
+        run(std::integral_constant<int, kSplitDefer>{});
     } else {
-      producer_item<down, kSplit>(a, item, tr, lds, words, late, hook);
+      run(std::integral_constant<int, kSplit>{});
     }
     if (tid == 0) next_publish(a, nx, end, words);
     __syncthreads();
@@ -845,63 +908,66 @@ __global__ __launch_bounds__(kProducerThreads, 1) void producer_kernel(ProducerA
 
 // ---------------------------------------------------------------------------
 // Tail: the split tile rows of a kModeDeferTail down launch.  Their parts only stored fp32
-// partials; here each workgroup pass takes one of a tile's 64 accumulator blocks, issues the
-// loads of all its parts at once, adds them in part order from part 0 -- exactly the sums the
-// last-arriving part would form -- and stores those outputs where the down epilogue would (Y
-// at device scope, or the local receive buffer).  The last of a tile's 64 passes raises its
-// flag.  Thread tid takes the positions producer thread tid held, so its loads are the 8-byte
-// words that thread stored.
+// partials; here each workgroup pass takes four adjacent 16x16 blocks of a tile (one per wave:
+// 16 rows x 64 columns), issues the loads of all their parts at once, adds them in part order from
+// part 0, and stores those outputs where the down epilogue would (Y at device scope, or the local
+// receive buffer).  Bound by the read of the parts: one 16-byte load per lane and part, as many as the
+// tile has parts (with 8-byte words and always kMaxSplitK loads, parts past the count re-read, a
+// two-part tail of 128 tiles took 46 us; it takes 18).  The last of a tile's 64 passes raises its flag.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kProducerThreads) void tail_kernel(TailArgs ta) {
   const ProducerArgs& a = ta.p;
   __builtin_amdgcn_s_setprio(3);  // ahead of consumer waves on shared CUs, like the producer
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wn = wave & 1, wm = wave >> 1, lr = lane & 31, lk = lane >> 5;
+  const int lr = lane & 15, lk = lane >> 4;
   const int dpr = a.down_per_row;
   const int64_t H = a.H;
-  constexpr int kBlocks = 64;
+  constexpr int kBlocks = (kTileM / 16) * (kDownTileN / 64);  // passes of a whole tile
   const int64_t n_pass = (int64_t)*ta.n_split_rows * dpr * kBlocks;
   const bool direct = (a.mode & kModeLocalDirect) != 0;
   const bool signal = (a.mode & kModeSignal) != 0;
   const bool direct_all = (a.mode & kModeDirectAll) != 0;
-  constexpr int kPartU64 = kProducerThreads * 128;
-  // The parts were stored by the previous launch at the coherence point; the launch's own
-  // acquire makes them visible, so no fence (an L2 invalidate per workgroup) is needed here.
+  // The parts were stored by the previous launch; the launch's own acquire makes them visible,
+  // so no fence (an L2 invalidate per workgroup) is needed here.
   for (int64_t pr = blockIdx.x; pr < n_pass; pr += gridDim.x) {
     const int t = ta.tail_rows[pr / (dpr * kBlocks)];
     const int col = (int)(pr / kBlocks % dpr), b = (int)(pr % kBlocks);
     const TileRow tr = a.tile_rows[t];
     const int S = tr.split;
-    const uint64_t* src = (const uint64_t*)a.partials + ((size_t)tr.part_base + (size_t)col * S) * kPartU64 +
-                          (2 * b) * kProducerThreads + tid;
-    // Every part's two words in flight together (a part past the count re-reads the last one
-    // and is not added).
-    uint64_t lo[kMaxSplitK], hi[kMaxSplitK];
-#pragma unroll
-    for (int p = 0; p < kMaxSplitK; ++p) {
-      const size_t o = (size_t)min(p, S - 1) * kPartU64;
-      lo[p] = src[o];
-      hi[p] = src[o + kProducerThreads];
-    }
-    float s0 = __uint_as_float((uint32_t)lo[0]), s1 = __uint_as_float((uint32_t)(lo[0] >> 32));
-    float s2 = __uint_as_float((uint32_t)hi[0]), s3 = __uint_as_float((uint32_t)(hi[0] >> 32));
-#pragma unroll
-    for (int p = 1; p < kMaxSplitK; ++p)
-      if (p < S) {
-        s0 += __uint_as_float((uint32_t)lo[p]);
-        s1 += __uint_as_float((uint32_t)(lo[p] >> 32));
-        s2 += __uint_as_float((uint32_t)hi[p]);
-        s3 += __uint_as_float((uint32_t)(hi[p] >> 32));
-      }
-    const int i = b >> 4, j = (b >> 2) & 3, q = b & 3;
-    const int m = wm * 128 + j * 32 + lr;
-    const int n = col * kDownTileN + wn * 128 + i * 32 + 8 * q + 4 * lk;
+    const int rb = b / (kDownTileN / 64), cb = (b % (kDownTileN / 64)) * 4 + wave;
+    const f32x4* src = (const f32x4*)a.partials + ((size_t)tr.part_base + (size_t)col * S) * kPartQuads +
+                       (size_t)(rb * (kDownTileN / 16) + cb) * 64 + lane;
+    const int m = rb * 16 + lr;
+    const int n = col * kDownTileN + cb * 16 + 4 * lk;
     const int lrow = tr.lrow0 + m;
     const int rank = a.row_rank[lrow];
+    const int slot = a.row_slot[lrow];
+    // Every part's quad in flight together, in the smallest of three batch sizes that holds the
+    // count (a part past it re-reads the last one and is not added).
+    f32x4 s;
+    auto add_parts = [&](auto np) {
+      constexpr int kP = decltype(np)::value;
+      f32x4 v[kP];
+#pragma unroll
+      for (int p = 0; p < kP; ++p) v[p] = src[(size_t)min(p, S - 1) * kPartQuads];
+      s = v[0];
+#pragma unroll
+      for (int p = 1; p < kP; ++p)
+        if (p < S) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) s[q] += v[p][q];
+        }
+    };
+    if (S <= 2)
+      add_parts(std::integral_constant<int, 2>{});
+    else if (S <= 4)
+      add_parts(std::integral_constant<int, 4>{});
+    else
+      add_parts(std::integral_constant<int, kMaxSplitK>{});
     if (rank >= 0 && n < H) {
-      const uint64_t v = (uint64_t)pack_bf16x2(s0, s1) | ((uint64_t)pack_bf16x2(s2, s3) << 32);
+      const uint64_t v = (uint64_t)pack_bf16x2(s[0], s[1]) | ((uint64_t)pack_bf16x2(s[2], s[3]) << 32);
       if (direct_all || (direct && rank == a.self_rank)) {
-        *(__attribute__((address_space(1))) uint64_t*)(a.ret[rank] + (int64_t)a.row_slot[lrow] * H + n) = v;
+        *(__attribute__((address_space(1))) uint64_t*)(a.ret[rank] + (int64_t)slot * H + n) = v;
         count_words(a.wcount, lrow, 1);
       } else if (signal)
         store8_device(a.y + (int64_t)lrow * H + n, v);
