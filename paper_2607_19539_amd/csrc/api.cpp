@@ -482,6 +482,7 @@ ProducerArgs producer_args(moe_stage_s* h, const BlobLayout& lay, const void* x,
   a.self_rank = h->cfg.self_rank;
   a.down_per_row = h->down_per_row;
   a.mode = mode;
+  a.compact = (!h->last_overlapped || h->cfg.band_rows <= 1) ? 1 : 0;  // the baseline's layout has no band padding
   a.split_k = h->cfg.down_split_k;
   a.partials = h->partials;
   a.arrivals = h->arrivals;

@@ -354,8 +354,113 @@ __device__ __forceinline__ void tile_mma(uint8_t* __restrict__ lds, DmaRows<kDma
   wait_vm_and_barrier<0>();
 }
 
+// ---------------------------------------------------------------------------
+// One output tile of 256 weight rows x 16*kNB token rows (kNB 4 or 2: at most 64 or 32 routed rows).
+// Such a tile reads far more weights than it multiplies: its time is the weight stream, from HBM
+// where each expert has few rows.  So the ring is four whole K steps of 32 KiB of weights and the
+// few tokens beside them (three in flight, about 100 KiB per compute unit, where 8 TB/s over 256
+// compute units at a loaded latency of 2-3 us asks for 60-90 KiB), one barrier per K step.  Each wave
+// takes 64 weight rows and every token row, so no weight fragment is read from LDS twice:
+// acc[i][j] holds n = (wave/2)*128 + (i/2)*64 + (wave%2)*32 + (i%2)*16 + 4*(lane/16) + r (a gate
+// row block and its up rows in the same wave), m = j*16 + lane%16.
+// ---------------------------------------------------------------------------
+template <int kNB, class Late>
+__device__ __forceinline__ void narrow_mma(uint8_t* __restrict__ lds, DmaRows<kDmaPerThread>& w, DmaRows<kNB / 2>& x,
+                                           int K, f32x4 (&acc)[4][kNB], Late&& late) {
+  static_assert(kNB == 2 || kNB == 4, "token fragments per wave");
+  constexpr int kStages = 4;
+  constexpr uint32_t kStageBytes = kBlockBytes + 16 * kNB * kRowBytes;
+  static_assert(kStages * kStageBytes <= (uint32_t)kLdsBytes, "ring of K steps");
+  constexpr int kDmaX = kNB / 2;
+  constexpr int kDmaStage = kDmaPerThread + kDmaX;
+  const int tid = item_thread(), lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const uint32_t lsw = swz(lr);
+  const uint32_t lane_chunk = (uint32_t)lr * kRowBytes + (((uint32_t)lk ^ lsw) << 4);
+  const uint32_t a_lane = (uint32_t)((wave >> 1) * 128 + (wave & 1) * 32) * kRowBytes + lane_chunk;
+  const uint32_t b_lane = (uint32_t)kBlockBytes + lane_chunk;
+
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < kNB; ++j) acc[i][j] = f32x4{};
+
+  const int nk = K / kTileK;
+  const uint32_t lds_w = lds_addr(lds) + (uint32_t)wave * kDmaPerThread * 1024;
+  const uint32_t lds_x = lds_addr(lds) + kBlockBytes + (uint32_t)wave * kDmaX * 1024;
+  uint32_t st_load = 0, st_use = 0;  // ring offsets of the next step to fetch and to multiply
+  auto next = [](uint32_t st) { return st == (kStages - 1) * kStageBytes ? 0u : st + kStageBytes; };
+  auto load = [&]() {
+    static_for<kDmaPerThread>([&](auto q) {
+      dma16<decltype(q)::value * 1024>(w.base, w.off[decltype(q)::value], lds_w + st_load);
+    });
+    static_for<kDmaX>([&](auto q) {
+      dma16<decltype(q)::value * 1024>(x.base, x.off[decltype(q)::value], lds_x + st_load);
+    });
+    w.base += w.step;
+    x.base += x.step;
+    st_load = next(st_load);
+  };
+  auto multiply = [&]() {
+    const uint32_t st = st_use;
+    st_use = next(st_use);
+    bf16x8 fa[2][4], fb[2][kNB];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int j = 0; j < kNB; ++j)
+        fb[kk][j] = *(const bf16x8*)(lds + ((b_lane ^ ((uint32_t)kk << 6)) + st + j * 16 * kRowBytes));
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        fa[kk][i] = *(const bf16x8*)(lds + ((a_lane ^ ((uint32_t)kk << 6)) + st + ((i >> 1) * 64 + (i & 1) * 16) * kRowBytes));
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < kNB; ++j) mfma16(acc[i][j], fa[kk][i], fb[kk][j]);
+  };
+  for (int ks = 0; ks < min(nk, kStages - 1); ++ks) load();
+  int ks = 0;
+  for (; ks + kStages - 1 < nk; ++ks) {
+    wait_vm_and_barrier<2 * kDmaStage>();  // step ks visible; every wave has read step ks-1
+    load();
+    multiply();
+  }
+  late();  // three K steps (or fewer) before the end
+  if (ks + 2 < nk) {
+    wait_vm_and_barrier<2 * kDmaStage>();
+    multiply();
+    ++ks;
+  }
+  if (ks + 1 < nk) {
+    wait_vm_and_barrier<kDmaStage>();
+    multiply();
+  }
+  wait_vm_and_barrier<0>();
+  multiply();
+  mfma_drain(acc);
+  // All waves are done reading LDS before the epilogue or the next tile reuses it.
+  wait_vm_and_barrier<0>();
+}
+
+// Token rows a tile row's items compute: the smallest of 32, 64, 128, 192 and 256 that holds its
+// routed rows.  Padding rows follow the routed ones when owner groups are not padded (a.compact),
+// so the rest of the tile row is nobody's output; with band padding in between, every row is taken.
+// Both launches decide alike, and the down launch reads only activation rows that were stored.
+// The time of a height is its products from 128 rows up and its weight stream below, so the narrow
+// tiles end at 64.  Whole tile rows only, then these heights: 8 rows in each of 32 experts (H 7168,
+// F 2048) 700 -> 566 us, 16 in each of two (H 4096, F 14336) 231 -> 194, 256 on average in each of 64
+// (H 1024, F 4096; half of the tile rows are remainders) 742 -> 681.
+__device__ __forceinline__ int tile_height(const ProducerArgs& a, const TileRow& tr) {
+  if (!a.compact || tr.nvalid > 192) return 256;
+  return tr.nvalid <= 32 ? 32 : tr.nvalid <= 64 ? 64 : tr.nvalid <= 128 ? 128 : 192;
+}
+
 // One work item; `down` selects a down-projection tile (otherwise a fused gate/up tile), kRows the
-// token rows computed.  kSplit (down tiles only) selects the K-part count at
+// token rows computed (see tile_height).  kSplit (down tiles only) selects the K-part count at
 // compile time: 1 = whole tiles, 2..4 = that many parts, 0 = the count of the item's tile row,
 // kSplitDefer = a part that only stores its sums for the tail kernel.  Each combination is its own
 // instantiation so the register allocator sees one straight path: a kernel holding two
@@ -371,8 +476,9 @@ constexpr int kSplitDefer = -2;
 template <bool down, int kSplit, int kRows, class Late, class Hook>
 __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t item, const TileRow& tr,
                                               uint8_t* lds, uint32_t* words, Late&& late, Hook&& hook) {
-  constexpr int kNI = 8;           // weight fragments per wave
-  constexpr int kNJ = kRows / 32;  // token fragments per wave
+  constexpr bool kNarrow = kRows <= 64;
+  constexpr int kNI = kNarrow ? 4 : 8;                  // weight fragments per wave
+  constexpr int kNJ = kNarrow ? kRows / 16 : kRows / 32;  // token fragments per wave
   constexpr int kDmaX = kRows / 32;                     // token DMA instructions per wave
   const int tid = item_thread(), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave: keeps bases scalar
@@ -383,8 +489,11 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
   const int64_t H = a.H, F = a.F;
   const int e = tr.expert, lrow0 = tr.lrow0;
   // Where accumulator quad (i, j) lies in the tile: its first weight row and its token row.
-  auto quad_n = [&](int i) { return (wave & 1) * 128 + i * 16 + 4 * lk; };
-  auto quad_m = [&](int j) { return (wave >> 1) * (kRows / 2) + j * 16 + lr; };
+  auto quad_n = [&](int i) {
+    return kNarrow ? (wave >> 1) * 128 + (i >> 1) * 64 + (wave & 1) * 32 + (i & 1) * 16 + 4 * lk
+                   : (wave & 1) * 128 + i * 16 + 4 * lk;
+  };
+  auto quad_m = [&](int j) { return (kNarrow ? 0 : (wave >> 1) * (kRows / 2)) + j * 16 + lr; };
   // Operand rows: DMA instruction i of a wave fills weight-tile rows wave*64 + i*8 .. +7 and
   // token-tile rows (wave*kDmaX + i)*8 .. +7.  The bases are wave-uniform (scalar registers) and the
   // offsets from them below 2^32: at most 256 rows of at most 2^17 bytes, or gathered token rows of
@@ -449,7 +558,10 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
   f32x4 acc[kNI][kNJ];
   w.base += (size_t)(kbeg / kTileK) * w.step;
   x.base += (size_t)(kbeg / kTileK) * x.step;
-  tile_mma<kNJ>(lds, w, x, klen, acc, late);
+  if constexpr (kNarrow)
+    narrow_mma<kNJ>(lds, w, x, klen, acc, late);
+  else
+    tile_mma<kNJ>(lds, w, x, klen, acc, late);
 
   if constexpr (!down) {
     // Gated activation a = bf16(silu(g) * u): lane values -> LDS tile [kRows rows][128 features].
@@ -870,17 +982,33 @@ __global__ __launch_bounds__(kProducerThreads, 1) void producer_kernel(ProducerA
     auto hook = [&]() {
       if (tid == 0) next_resolve(a, nx, end);
     };
-    auto run = [&](auto split) {
-      producer_item<down, decltype(split)::value, kTileM>(a, item, tr, lds, words, late, hook);
+    auto run = [&](auto split, auto rows) {
+      producer_item<down, decltype(split)::value, decltype(rows)::value>(a, item, tr, lds, words, late, hook);
+    };
+    // As many token rows as the tile row needs (explicit splits: always the whole tile row).
+    auto by_height = [&](auto split) {
+      const int h = tile_height(a, tr);
+      if (h == 256)
+        run(split, std::integral_constant<int, 256>{});
+      else if (h == 192)
+        run(split, std::integral_constant<int, 192>{});
+      else if (h == 128)
+        run(split, std::integral_constant<int, 128>{});
+      else if (h == 64)
+        run(split, std::integral_constant<int, 64>{});
+      else
+        run(split, std::integral_constant<int, 32>{});
     };
     if constexpr (kSplit < 0) {
       // Split per tile row: whole tiles take the plain epilogue, split rows only store their parts.
       if (tr.split == 1)
-        run(std::integral_constant<int, 1>{});
+        by_height(std::integral_constant<int, 1>{});
       else
-        run(std::integral_constant<int, kSplitDefer>{});
+        by_height(std::integral_constant<int, kSplitDefer>{});
+    } else if constexpr (kSplit == 1) {
+      by_height(std::integral_constant<int, 1>{});
     } else {
-      run(std::integral_constant<int, kSplit>{});
+      run(std::integral_constant<int, kSplit>{}, std::integral_constant<int, kTileM>{});
     }
     if (tid == 0) next_publish(a, nx, end, words);
     __syncthreads();
@@ -913,7 +1041,7 @@ __global__ __launch_bounds__(kProducerThreads, 1) void producer_kernel(ProducerA
 // part 0, and stores those outputs where the down epilogue would (Y at device scope, or the local
 // receive buffer).  Bound by the read of the parts: one 16-byte load per lane and part, as many as the
 // tile has parts (with 8-byte words and always kMaxSplitK loads, parts past the count re-read, a
-// two-part tail of 128 tiles took 46 us; it takes 18).  The last of a tile's 64 passes raises its flag.
+// two-part tail of 128 tiles took 46 us; it takes 18).  The last of a tile's passes that hold routed rows raises its flag.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kProducerThreads) void tail_kernel(TailArgs ta) {
   const ProducerArgs& a = ta.p;
@@ -934,7 +1062,10 @@ __global__ __launch_bounds__(kProducerThreads) void tail_kernel(TailArgs ta) {
     const int col = (int)(pr / kBlocks % dpr), b = (int)(pr % kBlocks);
     const TileRow tr = a.tile_rows[t];
     const int S = tr.split;
+    // Row blocks past the routed rows were never computed (see tile_height).
+    const int n_rb = a.compact ? (tr.nvalid + 15) / 16 : kTileM / 16;
     const int rb = b / (kDownTileN / 64), cb = (b % (kDownTileN / 64)) * 4 + wave;
+    if (rb >= n_rb) continue;
     const f32x4* src = (const f32x4*)a.partials + ((size_t)tr.part_base + (size_t)col * S) * kPartQuads +
                        (size_t)(rb * (kDownTileN / 16) + cb) * 64 + lane;
     const int m = rb * 16 + lr;
@@ -982,7 +1113,7 @@ __global__ __launch_bounds__(kProducerThreads) void tail_kernel(TailArgs ta) {
         const int tile = t * dpr + col;
         const uint32_t prev =
             __hip_atomic_fetch_add(&a.arrivals[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (prev + 1 == (uint32_t)kBlocks) {
+        if (prev + 1 == (uint32_t)(n_rb * (kDownTileN / 64))) {
           if (a.tile_ready) a.tile_ready[tile] = ticks();
           __hip_atomic_store(&a.flags[tile], a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }

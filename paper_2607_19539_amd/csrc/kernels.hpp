@@ -59,6 +59,7 @@ struct ProducerArgs {
   uint32_t epoch;
   int32_t H, F, self_rank, down_per_row;
   uint32_t mode;
+  int32_t compact;         // 1: a tile row's routed rows come first (no band padding between groups)
   int32_t split_k;         // K parts of every down tile; 0 = per tile row (TileRow::split)
   float* partials;         // fp32 part tiles (256 threads x 256) from TileRow::part_base on
   uint32_t* arrivals;      // [tiles] parts finished this run (zeroed by the init kernel)
