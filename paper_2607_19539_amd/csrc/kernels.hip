@@ -234,8 +234,8 @@ __device__ __forceinline__ void mfma_drain(f32x4 (&acc)[kNI][kNJ]) {
 // fragments are read under the first half's MFMAs, and the next sub-step's first token fragments
 // and each weight fragment, as its last MFMA has issued, under the second half's (64 vector
 // registers of operands where two buffers would take 128).  The DMAs go out where slots are free:
-// block 2ks+4 in the step's first half sub-step (its slot held K step ks-1's tokens), block 2ks+5
-// in the last one, after the barrier that ends every wave's reads of step ks.  That barrier also
+// block 2ks+4 in the step's first sub-step (its slot held K step ks-1's tokens), block 2ks+5
+// in its last quarter, after the barrier that ends every wave's reads of step ks.  That barrier also
 // waits for step ks+1's blocks, with only block 2ks+4 allowed in flight.  The last two K steps are
 // peeled so each wait count is a constant on a straight path.
 // ---------------------------------------------------------------------------
@@ -297,29 +297,40 @@ __device__ __forceinline__ void tile_mma(uint8_t* __restrict__ lds, DmaRows<kDma
 #pragma unroll
   for (int i = 0; i < 8; ++i) read_a(o0, 0, i);
 
+  // The weight block's DMAs go out over the step's first two quarters, one per two weight fragments:
+  // the address units take 16 cycles for each of the four waves' DMAs, so eight per wave in one
+  // quarter (512 cycles) fill them, and any delay holds up the wave's matrix instructions.  Against
+  // one quarter: the down launch of 18160 rows 1460 -> 1391 us, the gate/up launch of 48960 rows in 16
+  // experts (H 2048, F 1408) 418 -> 403; over three quarters the same (1390, 401), with less lead.
+  auto w_dma = [](int quarter, int i) { return quarter < 2 && i % 2 == 0 ? quarter * 4 + i / 2 : -1; };
   // First half of sub-step kk: reads its other token fragments; with kDma, block 2ks+4's DMAs.
-  auto half0 = [&](int kk, auto dma) {
+  auto half0 = [&](auto kkc, auto dma) {
+    constexpr int kk = decltype(kkc)::value;
     static_for<8 * kHJ>([&](auto p) {
       constexpr int i = decltype(p)::value / kHJ, j = decltype(p)::value % kHJ;
       constexpr int js = i & 1 ? kHJ - 1 - j : j;
-      constexpr bool fetch_w = decltype(dma)::value && j == 0;
-      if constexpr (fetch_w) dma_m0<i * 1024>(lds_w + o4);
+      constexpr int wq = decltype(dma)::value && j == kHJ / 2 ? w_dma(2 * kk, i) : -1;
+      if constexpr (wq >= 0) dma_m0<wq * 1024>(lds_w + o4);
       mfma16(acc[i][js], fa[i], fb[js]);
-      if constexpr (fetch_w) dma16_at_m0(w.base, w.off[i]);
+      if constexpr (wq >= 0) dma16_at_m0(w.base, w.off[wq]);
       if constexpr (j == 1 && i < kHJ) read_b(o1, kk, kHJ + i);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
   // Second half: with kRead, reads what the next sub-step (kk1, slots sa and sb) starts with; with
-  // kDma, block 2ks+5's DMAs.
-  auto half1 = [&](uint32_t sa, uint32_t sb, int kk1, auto rd, auto dma) {
+  // kDma, in the step's last quarter, block 2ks+5's DMAs.
+  auto half1 = [&](uint32_t sa, uint32_t sb, auto kk1c, auto rd, auto dma) {
+    constexpr int kk1 = decltype(kk1c)::value;
     static_for<8 * kHJ>([&](auto p) {
       constexpr int i = decltype(p)::value / kHJ, j = decltype(p)::value % kHJ;
       constexpr int js = kHJ + (i & 1 ? kHJ - 1 - j : j);
-      constexpr bool fetch_x = decltype(dma)::value && j == kHJ / 2 && i < kNJ;
+      constexpr bool fetch_x = decltype(dma)::value && kk1 == 0 && j == kHJ / 2 && i < kNJ;
+      constexpr int wq = decltype(dma)::value && kk1 == 1 && j == kHJ / 2 ? w_dma(1, i) : -1;
       if constexpr (fetch_x) dma_m0<i * 1024>(lds_x + o0);
+      if constexpr (wq >= 0) dma_m0<wq * 1024>(lds_w + o4);
       mfma16(acc[i][js], fa[i], fb[js]);
       if constexpr (fetch_x) dma16_at_m0(x.base, x.off[i]);
+      if constexpr (wq >= 0) dma16_at_m0(w.base, w.off[wq]);
       if constexpr (decltype(rd)::value) {
         if constexpr (j == 0 && i < kHJ) read_b(sb, kk1, i);
         if constexpr (j == kHJ - 1) read_a(sa, kk1, i);
@@ -332,11 +343,13 @@ __device__ __forceinline__ void tile_mma(uint8_t* __restrict__ lds, DmaRows<kDma
   auto step = [&](auto kind) {
     constexpr int kd = decltype(kind)::value;
     using steady = std::integral_constant<bool, kd == 0>;
-    half0(0, steady{});
-    half1(o0, o1, 1, std::true_type{}, std::false_type{});
-    half0(1, std::false_type{});
+    using first = std::integral_constant<int, 0>;
+    using second = std::integral_constant<int, 1>;
+    half0(first{}, steady{});
+    half1(o0, o1, second{}, std::true_type{}, steady{});
+    half0(second{}, std::false_type{});
     if constexpr (kd < 2) wait_vm_and_barrier<kd == 0 ? kDmaPerThread : 0>();  // step ks+1 visible, step ks's slots free
-    half1(o2, o3, 0, std::integral_constant<bool, (kd < 2)>{}, steady{});
+    half1(o2, o3, first{}, std::integral_constant<bool, (kd < 2)>{}, steady{});
     if constexpr (kd == 0) {
       w.base += w.step;
       x.base += x.step;
