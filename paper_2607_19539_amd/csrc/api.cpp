@@ -236,10 +236,10 @@ uint64_t watchdog_ticks(const moe_stage_s* h) {
   return (uint64_t)ms * 100000ull;  // wall clock runs at 100 MHz
 }
 
-// Resets the run counters on `stream` (and, before a device-built plan, the planner's scratch
-// and header), and advances the flag epoch.
-int enqueue_init(moe_stage_s* h, bool overlapped, bool dev, int32_t n_tile_rows, int64_t n_lrows,
-                 hipStream_t stream) {
+// What the run's reset does (and, before a device-built plan, with the planner's scratch and header),
+// and the flag epoch it begins.
+InitArgs init_args(moe_stage_s* h, bool overlapped, bool dev, int32_t n_tile_rows, int64_t n_lrows,
+                   uint32_t epoch) {
   const moe_stage_config_t& c = h->cfg;
   InitArgs ia{};
   ia.ctr = h->ctr;
@@ -254,7 +254,6 @@ int enqueue_init(moe_stage_s* h, bool overlapped, bool dev, int32_t n_tile_rows,
     ia.poison = h->y;
     ia.poison_elems = n_lrows * c.hidden;
   }
-  const uint32_t epoch = h->epoch + 1 == 0 ? 1 : h->epoch + 1;  // flags hold the epoch of the run that set them
   if (overlapped && (c.flags & MOE_TEST_CONSUMER_ONLY)) {
     ia.publish = h->flags;
     ia.n_publish = ia.n_arrivals;
@@ -265,9 +264,11 @@ int enqueue_init(moe_stage_s* h, bool overlapped, bool dev, int32_t n_tile_rows,
     ia.n_fill_ones = h->ws.fill_words;
     ia.plan_hdr = (PlanHeader*)(h->d_plan + h->cap_lay.hdr);
   }
-  HIP_TRY(h, launch_init(ia, stream));
-  h->epoch = epoch;
-  return MOE_OK;
+  return ia;
+}
+
+uint32_t next_epoch(const moe_stage_s* h) {  // flags hold the epoch of the run that set them
+  return h->epoch + 1 == 0 ? 1 : h->epoch + 1;
 }
 
 // Host arguments both planners check before anything is enqueued.
@@ -356,8 +357,9 @@ int prepare(moe_stage_s* h, bool overlapped, const void* x,
 
   HIP_TRY(h, hipMemcpyAsync(h->d_plan, hs, lay->total, hipMemcpyHostToDevice, stream));
   HIP_TRY(h, hipEventRecord(h->stage_free[si], stream));
-  rc = enqueue_init(h, overlapped, false, (int32_t)P.tile_rows.size(), P.n_lrows(), stream);
-  if (rc) return rc;
+  const uint32_t epoch = next_epoch(h);
+  HIP_TRY(h, launch_init(init_args(h, overlapped, false, (int32_t)P.tile_rows.size(), P.n_lrows(), epoch), stream));
+  h->epoch = epoch;
   h->last_lay = *lay;
   h->last_dev = false;
   h->dev_hdr_pending = false;
@@ -410,9 +412,6 @@ int prepare_device(moe_stage_s* h, bool overlapped, const void* x, const int32_t
     HIP_TRY(h, hipMemcpyAsync(h->d_plan + lay->ret + sizeof(void*) * R, return_rows, sizeof(int64_t) * R,
                               hipMemcpyHostToDevice, stream));
   }
-  rc = enqueue_init(h, overlapped, true, h->max_tile_rows, h->max_lrows, stream);
-  if (rc) return rc;
-
   DevPlanArgs a{};
   a.off = off;
   a.src = src;
@@ -446,7 +445,10 @@ int prepare_device(moe_stage_s* h, bool overlapped, const void* x, const int32_t
   a.groups = (Group*)(h->d_plan + lay->groups);
   a.tail_rows = (int32_t*)(h->d_plan + lay->tail);
   a.ws = h->ws;
-  HIP_TRY(h, launch_devplan(a, h->max_items, h->num_cus, stream));
+  const uint32_t epoch = next_epoch(h);
+  HIP_TRY(h, launch_devplan(a, init_args(h, overlapped, true, h->max_tile_rows, h->max_lrows, epoch), h->max_items,
+                            h->num_cus, stream));
+  h->epoch = epoch;
   h->last.plan_us =
       std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count();
   h->last_lay = *lay;

@@ -24,6 +24,7 @@
 
 #include <type_traits>
 
+#include "init_device.hpp"
 #include "kernels.hpp"
 
 namespace moe {
@@ -1547,48 +1548,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a) {
 }
 
 __global__ __launch_bounds__(256) void init_kernel(InitArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  if (i == 0) {
-    for (int x = 0; x < kXcds; ++x) {
-      a.ctr->gu_next[x] = 0;
-      a.ctr->down_next[x] = 0;
-    }
-    a.ctr->seg_next = 0;
-    a.ctr->gu_active = 0;
-    a.ctr->down_active = 0;
-    a.ctr->poll_iters = 0;
-    a.ctr->wait_ticks = 0;
-    a.ctr->n_units = 0;
-    a.ctr->cons_exit = 0;
-    a.ctr->units_pub = 0;
-    a.ctr->prod_t0 = ~0ull;
-    a.ctr->prod_t1 = 0;
-    a.ctr->n_abandoned = 0;
-    if (a.plan_hdr) {
-      a.plan_hdr->status = 0;
-      a.plan_hdr->bad_row = INT_MAX;
-    }
-  }
-  if (a.fill_ones)
-    for (int64_t j = i; j < a.n_fill_ones; j += stride) a.fill_ones[j] = ~0u;
-  for (int64_t j = i; j < a.n_arrivals; j += stride) a.arrivals[j] = 0;
-  if (a.wcount)
-    for (int64_t j = i; j < a.n_wcount; j += stride) a.wcount[j] = 0;
-  if (a.tile_ready)
-    for (int64_t j = i; j < a.n_arrivals; j += stride) a.tile_ready[j] = 0;
-  if (a.simd_waves)
-    for (int64_t j = i; j < kWaveCounters; j += stride) a.simd_waves[j] = 0;
-  // Published flags are stored as the producer raises them (relaxed, agent scope): a plain store
-  // would sit in this XCD's L2, and the consumer's polls on other XCDs would not see it until the
-  // line is written back.
-  if (a.publish)
-    for (int64_t j = i; j < a.n_publish; j += stride)
-      __hip_atomic_store(&a.publish[j], a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (a.poison) {
-    const u32x4 nan = {0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u};
-    for (int64_t j = i; j < a.poison_elems / 8; j += stride) ((u32x4*)a.poison)[j] = nan;
-  }
+  reset_run(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
 hipError_t launch_init(const InitArgs& a, hipStream_t s) {

@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernels.hpp"
 #include "plan_types.hpp"
 
 namespace moe {
@@ -80,8 +81,8 @@ size_t devplan_ws_bytes(int32_t E_l, int32_t R, int32_t max_rows, int32_t max_ti
 DevPlanWs devplan_ws_carve(void* base, int32_t E_l, int32_t R, int32_t max_rows, int32_t max_tile_rows,
                            int32_t down_per_row, int64_t max_lrows, int64_t max_items);
 
-// Enqueues the planner kernels on `s`.  The init kernel must already have filled the
-// all-ones range of the scratch and reset the header (status 0, bad_row INT32_MAX).
-hipError_t launch_devplan(const DevPlanArgs& a, int64_t max_items, int num_cus, hipStream_t s);
+// Enqueues the run's reset and the planner kernels on `s`.  `init` resets the header (status 0,
+// bad_row INT32_MAX) and fills the all-ones range of the scratch.
+hipError_t launch_devplan(const DevPlanArgs& a, const InitArgs& init, int64_t max_items, int num_cus, hipStream_t s);
 
 }  // namespace moe
