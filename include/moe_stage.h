@@ -240,7 +240,8 @@ int moe_stage_run(moe_stage_t h, const void* dispatched_x, const int32_t* expert
 /*
  * Non-overlapped baseline (paper Section 4.1.3: expert compute, then the
  * whole return transfer): the same producer on all compute units with no
- * signaling, then one scatter kernel that copies every routed row to its slot.
+ * signaling, then one scatter kernel that copies every routed row to its slot
+ * (rows of tail tiles split over K: it adds the parts straight into their slots).
  */
 int moe_stage_run_serial(moe_stage_t h, const void* dispatched_x, const int32_t* expert_offsets,
                          const int32_t* row_src_rank, const int32_t* row_slot, const void* w1,

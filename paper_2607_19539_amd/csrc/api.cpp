@@ -1029,8 +1029,10 @@ static int run_serial(moe_stage_t h, bool dev, const void* x, const int32_t* off
   if (!known || h->plan.n_gu > 0) HIP_TRY(h, launch_producer(pgu, false, pgrid, stream));
   if (tr) HIP_TRY(h, hipEventRecord(tr->ev[6], stream));
   if (!known || h->plan.n_down > 0) HIP_TRY(h, launch_producer(pa, true, pgrid, stream));
-  if ((pa.mode & kModeDeferTail) && (!known || h->plan.n_split_rows > 0))
-    HIP_TRY(h, launch_tail(tail_args(h, lay, pa), kTailGrid, stream));
+  // Split tail tiles: the return copy adds their parts straight into the rows' slots; without one
+  // (direct_all) a tail launch does.
+  const bool tail = (pa.mode & kModeDeferTail) && (!known || h->plan.n_split_rows > 0);
+  if (tail && direct_all) HIP_TRY(h, launch_tail(tail_args(h, lay, pa), kTailGrid, stream));
   if (tr) HIP_TRY(h, hipEventRecord(tr->ev[2], stream));
   ScatterArgs sa{};
   sa.y = h->y;
@@ -1042,8 +1044,14 @@ static int run_serial(moe_stage_t h, bool dev, const void* x, const int32_t* off
   sa.wcount = h->wcount;
   if (tr) HIP_TRY(h, hipEventRecord(tr->ev[4], stream));
   const int64_t scatter_rows = known ? h->plan.n_lrows() : h->max_lrows;
-  if (scatter_rows > 0 && !direct_all)
-    HIP_TRY(h, launch_scatter(sa, (int)std::min<int64_t>(scatter_rows, (int64_t)h->num_cus * 8), stream));
+  if (scatter_rows > 0 && !direct_all) {
+    TailArgs ta{};
+    if (tail) {
+      ta = tail_args(h, lay, pa);
+      ta.p.mode |= kModeDirectAll;
+    }
+    HIP_TRY(h, launch_scatter(sa, ta, (int)std::min<int64_t>(scatter_rows, (int64_t)h->num_cus * 8), stream));
+  }
   if (tr) {
     HIP_TRY(h, hipEventRecord(tr->ev[5], stream));
     tr->kind = 1;

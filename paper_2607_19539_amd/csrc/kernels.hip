@@ -10,7 +10,7 @@
 //  * consumer: persistent kernel on its own compute units (Section 3.3.3)
 //    that polls the flags of whole segments (Section 3.3.2) and copies each
 //    ready segment into its destination receive buffer.
-//  * scatter: the non-overlapped baseline's bulk return copy.
+//  * scatter: the non-overlapped baseline's bulk return copy (and its split tail tiles' sums).
 //  * init: resets the per-run counters (a kernel, not a memset, so the
 //    sequence stays capturable).
 //
@@ -1057,87 +1057,98 @@ __global__ __launch_bounds__(kProducerThreads, 1) void producer_kernel(ProducerA
 // tile has parts (with 8-byte words and always kMaxSplitK loads, parts past the count re-read, a
 // two-part tail of 128 tiles took 46 us; it takes 18).  The last of a tile's passes that hold routed rows raises its flag.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kProducerThreads) void tail_kernel(TailArgs ta) {
+constexpr int kTailPasses = (kTileM / 16) * (kDownTileN / 64);  // passes of a whole tile
+
+__device__ __forceinline__ int64_t tail_passes(const TailArgs& ta) {
+  return (int64_t)*ta.n_split_rows * ta.p.down_per_row * kTailPasses;
+}
+
+__device__ __forceinline__ void tail_pass(const TailArgs& ta, int64_t pr) {
   const ProducerArgs& a = ta.p;
-  __builtin_amdgcn_s_setprio(3);  // ahead of consumer waves on shared CUs, like the producer
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   const int dpr = a.down_per_row;
   const int64_t H = a.H;
-  constexpr int kBlocks = (kTileM / 16) * (kDownTileN / 64);  // passes of a whole tile
-  const int64_t n_pass = (int64_t)*ta.n_split_rows * dpr * kBlocks;
   const bool direct = (a.mode & kModeLocalDirect) != 0;
   const bool signal = (a.mode & kModeSignal) != 0;
   const bool direct_all = (a.mode & kModeDirectAll) != 0;
   // The parts were stored by the previous launch; the launch's own acquire makes them visible,
   // so no fence (an L2 invalidate per workgroup) is needed here.
-  for (int64_t pr = blockIdx.x; pr < n_pass; pr += gridDim.x) {
-    const int t = ta.tail_rows[pr / (dpr * kBlocks)];
-    const int col = (int)(pr / kBlocks % dpr), b = (int)(pr % kBlocks);
-    const TileRow tr = a.tile_rows[t];
-    const int S = tr.split;
-    // Row blocks past the routed rows were never computed (see tile_height).
-    const int n_rb = a.compact ? (tr.nvalid + 15) / 16 : kTileM / 16;
-    const int rb = b / (kDownTileN / 64), cb = (b % (kDownTileN / 64)) * 4 + wave;
-    if (rb >= n_rb) continue;
-    const f32x4* src = (const f32x4*)a.partials + ((size_t)tr.part_base + (size_t)col * S) * kPartQuads +
-                       (size_t)(rb * (kDownTileN / 16) + cb) * 64 + lane;
-    const int m = rb * 16 + lr;
-    const int n = col * kDownTileN + cb * 16 + 4 * lk;
-    const int lrow = tr.lrow0 + m;
-    const int rank = a.row_rank[lrow];
-    const int slot = a.row_slot[lrow];
-    // Every part's quad in flight together, in the smallest of three batch sizes that holds the
-    // count (a part past it re-reads the last one and is not added).
-    f32x4 s;
-    auto add_parts = [&](auto np) {
-      constexpr int kP = decltype(np)::value;
-      f32x4 v[kP];
+  const int t = ta.tail_rows[pr / (dpr * kTailPasses)];
+  const int col = (int)(pr / kTailPasses % dpr), b = (int)(pr % kTailPasses);
+  const TileRow tr = a.tile_rows[t];
+  const int S = tr.split;
+  // Row blocks past the routed rows were never computed (see tile_height).
+  const int n_rb = a.compact ? (tr.nvalid + 15) / 16 : kTileM / 16;
+  const int rb = b / (kDownTileN / 64), cb = (b % (kDownTileN / 64)) * 4 + wave;
+  if (rb >= n_rb) return;
+  const f32x4* src = (const f32x4*)a.partials + ((size_t)tr.part_base + (size_t)col * S) * kPartQuads +
+                     (size_t)(rb * (kDownTileN / 16) + cb) * 64 + lane;
+  const int m = rb * 16 + lr;
+  const int n = col * kDownTileN + cb * 16 + 4 * lk;
+  const int lrow = tr.lrow0 + m;
+  const int rank = a.row_rank[lrow];
+  const int slot = a.row_slot[lrow];
+  // Every part's quad in flight together, in the smallest of three batch sizes that holds the
+  // count (a part past it re-reads the last one and is not added).
+  f32x4 s;
+  auto add_parts = [&](auto np) {
+    constexpr int kP = decltype(np)::value;
+    f32x4 v[kP];
 #pragma unroll
-      for (int p = 0; p < kP; ++p) v[p] = src[(size_t)min(p, S - 1) * kPartQuads];
-      s = v[0];
+    for (int p = 0; p < kP; ++p) v[p] = src[(size_t)min(p, S - 1) * kPartQuads];
+    s = v[0];
 #pragma unroll
-      for (int p = 1; p < kP; ++p)
-        if (p < S) {
+    for (int p = 1; p < kP; ++p)
+      if (p < S) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) s[q] += v[p][q];
-        }
-    };
-    if (S <= 2)
-      add_parts(std::integral_constant<int, 2>{});
-    else if (S <= 4)
-      add_parts(std::integral_constant<int, 4>{});
+        for (int q = 0; q < 4; ++q) s[q] += v[p][q];
+      }
+  };
+  if (S <= 2)
+    add_parts(std::integral_constant<int, 2>{});
+  else if (S <= 4)
+    add_parts(std::integral_constant<int, 4>{});
+  else
+    add_parts(std::integral_constant<int, kMaxSplitK>{});
+  if (rank >= 0 && n < H) {
+    const uint64_t v = (uint64_t)pack_bf16x2(s[0], s[1]) | ((uint64_t)pack_bf16x2(s[2], s[3]) << 32);
+    if (direct_all || (direct && rank == a.self_rank)) {
+      *(__attribute__((address_space(1))) uint64_t*)(a.ret[rank] + (int64_t)slot * H + n) = v;
+      count_words(a.wcount, lrow, 1);
+    } else if (signal)
+      store8_device(a.y + (int64_t)lrow * H + n, v);
     else
-      add_parts(std::integral_constant<int, kMaxSplitK>{});
-    if (rank >= 0 && n < H) {
-      const uint64_t v = (uint64_t)pack_bf16x2(s[0], s[1]) | ((uint64_t)pack_bf16x2(s[2], s[3]) << 32);
-      if (direct_all || (direct && rank == a.self_rank)) {
-        *(__attribute__((address_space(1))) uint64_t*)(a.ret[rank] + (int64_t)slot * H + n) = v;
-        count_words(a.wcount, lrow, 1);
-      } else if (signal)
-        store8_device(a.y + (int64_t)lrow * H + n, v);
-      else
-        *(__attribute__((address_space(1))) uint64_t*)(a.y + (int64_t)lrow * H + n) = v;
-    }
-    if (signal && (tr.has_remote || !direct)) {
-      // Every wave's stores have completed before the pass counts itself in; the pass that
-      // completes the tile raises the flag.
-      wait_vm_and_barrier<0>();
-      if (tid == 0) {
-        const int tile = t * dpr + col;
-        const uint32_t prev =
-            __hip_atomic_fetch_add(&a.arrivals[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (prev + 1 == (uint32_t)(n_rb * (kDownTileN / 64))) {
-          if (a.tile_ready) a.tile_ready[tile] = ticks();
-          __hip_atomic_store(&a.flags[tile], a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+      *(__attribute__((address_space(1))) uint64_t*)(a.y + (int64_t)lrow * H + n) = v;
+  }
+  if (signal && (tr.has_remote || !direct)) {
+    // Every wave's stores have completed before the pass counts itself in; the pass that
+    // completes the tile raises the flag.
+    wait_vm_and_barrier<0>();
+    if (tid == 0) {
+      const int tile = t * dpr + col;
+      const uint32_t prev =
+          __hip_atomic_fetch_add(&a.arrivals[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (prev + 1 == (uint32_t)(n_rb * (kDownTileN / 64))) {
+        if (a.tile_ready) a.tile_ready[tile] = ticks();
+        __hip_atomic_store(&a.flags[tile], a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
-  if (a.wg_rec && n_pass > 0) {  // timestamped runs: the producer ends with its last tail pass
-    wait_vm_and_barrier<0>();
-    if (tid == 0) __hip_atomic_fetch_max(&a.ctr->prod_t1, ticks(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+}
+
+// Timestamped runs: the producer ends with its last tail pass.
+__device__ __forceinline__ void tail_done(const ProducerArgs& a) {
+  if (!a.wg_rec) return;
+  wait_vm_and_barrier<0>();
+  if (threadIdx.x == 0) __hip_atomic_fetch_max(&a.ctr->prod_t1, ticks(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ __launch_bounds__(kProducerThreads) void tail_kernel(TailArgs ta) {
+  __builtin_amdgcn_s_setprio(3);  // ahead of consumer waves on shared CUs, like the producer
+  const int64_t n_pass = tail_passes(ta);
+  for (int64_t pr = blockIdx.x; pr < n_pass; pr += gridDim.x) tail_pass(ta, pr);
+  if (n_pass > 0) tail_done(ta.p);
 }
 
 // ---------------------------------------------------------------------------
@@ -1532,18 +1543,36 @@ hipError_t launch_plain_copy(const ConsumerArgs& a, int grid, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Baseline bulk return: every routed row of the staged output to its slot.
+// Baseline bulk return: every routed row of the staged output to its slot.  The rows of split tail
+// tiles are not staged: their parts are added here, straight into their slots (one launch and one
+// pass over those rows less than a tail launch before it).  HBM-bound: a wave copies up to 256
+// 16-byte vectors of one row, up to four loads per lane in flight, whatever the row length (with a
+// workgroup per row, rows of 2 KiB left half of its threads idle and one load in flight).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a) {
-  const int64_t per_row = a.H / 8;
-  const int64_t n_lrows = *a.n_lrows;
-  for (int64_t r = blockIdx.x; r < n_lrows; r += gridDim.x) {
+__global__ __launch_bounds__(kProducerThreads) void scatter_kernel(ScatterArgs a, TailArgs ta) {
+  const int64_t n_pass = ta.tail_rows ? tail_passes(ta) : 0;
+  for (int64_t pr = blockIdx.x; pr < n_pass; pr += gridDim.x) tail_pass(ta, pr);
+  if (n_pass > 0) tail_done(ta.p);
+  constexpr int kU = 4;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int32_t per_row = a.H / 8, chunks = (per_row + 64 * kU - 1) / (64 * kU);
+  const int64_t n_units = *a.n_lrows * chunks;
+  // The last workgroups take the first rows: the first ones have tail passes.
+  for (int64_t u = (int64_t)(gridDim.x - 1 - blockIdx.x) * 4 + wave; u < n_units; u += (int64_t)gridDim.x * 4) {
+    const int32_t r = (int32_t)(u / chunks), c0 = (int32_t)(u - (int64_t)r * chunks) * 64 * kU;
     const int rank = a.row_rank[r];
-    if (rank < 0) continue;
-    const u32x4* src = (const u32x4*)(a.y + r * a.H);
+    if (rank < 0 || (n_pass > 0 && ta.p.tile_rows[r / kTileM].split > 1)) continue;
+    const u32x4* src = (const u32x4*)(a.y + (int64_t)r * a.H);
     g_u32x4* dst = (g_u32x4*)(a.ret[rank] + (int64_t)a.row_slot[r] * a.H);
-    for (int64_t i = threadIdx.x; i < per_row; i += blockDim.x) dst[i] = src[i];
-    if (threadIdx.x == 0) count_words(a.wcount, r, (uint32_t)(2 * per_row));
+    u32x4 v[kU];
+#pragma unroll
+    for (int k = 0; k < kU; ++k)
+      if (c0 + k * 64 + lane < per_row) v[k] = src[c0 + k * 64 + lane];
+#pragma unroll
+    for (int k = 0; k < kU; ++k)
+      if (c0 + k * 64 + lane < per_row) dst[c0 + k * 64 + lane] = v[k];
+    if (lane == 0) count_words(a.wcount, r, (uint32_t)(2 * (min(per_row, c0 + 64 * kU) - c0)));
   }
 }
 
@@ -1628,8 +1657,8 @@ hipError_t launch_stamp(uint64_t* dst, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_scatter(const ScatterArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(scatter_kernel, dim3(grid), dim3(256), 0, s, a);
+hipError_t launch_scatter(const ScatterArgs& a, const TailArgs& tail, int grid, hipStream_t s) {
+  hipLaunchKernelGGL(scatter_kernel, dim3(grid), dim3(kProducerThreads), 0, s, a, tail);
   return hipGetLastError();
 }
 
