@@ -22,14 +22,19 @@ __device__ __forceinline__ uint32_t to_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// Up to this many workgroups a call leaves compute units idle and its time is a chain of loads
+// (slots, rows, the next batch's): then one vector per thread, so a token spreads over more
+// workgroups, and with over four choices eight rows in flight instead of four.
+constexpr int64_t kFewWorkgroups = 512;
+
 // out[t] = bf16(sum_j gate[t, j] * recv[slot[t, j]]).
 // A workgroup covers kVec * 256 16-byte vectors of one token's row; each thread keeps
-// kVec * 8 fp32 sums.  The k choices are taken four at a time: the rows of a batch are
+// kVec * 8 fp32 sums.  The k choices are taken kBatch at a time: the rows of a batch are
 // loaded together, then added in choice order as separately rounded products and sums
 // (contraction off), so the result does not depend on the batching.  Out-of-range
 // slots are skipped and counted.
-template <int kVec>
-__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
+template <int kVec, int kBatch>
+__device__ __forceinline__ void combine_rows(const CombineArgs& a) {
 #pragma clang fp contract(off)
   const int64_t nvec = a.H / 8;
   const int64_t spans = (nvec + 256 * kVec - 1) / (256 * kVec);
@@ -43,12 +48,12 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
     for (int u = 0; u < kVec; ++u)
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[u][e] = 0.0f;
-    for (int j0 = 0; j0 < a.k; j0 += 4) {
-      u32x4 v[4][kVec];
-      float g[4];
-      bool ok[4];
+    for (int j0 = 0; j0 < a.k; j0 += kBatch) {
+      u32x4 v[kBatch][kVec];
+      float g[kBatch];
+      bool ok[kBatch];
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
+      for (int jj = 0; jj < kBatch; ++jj) {
         const int j = j0 + jj;
         const int32_t s = j < a.k ? a.slot[t * a.k + j] : -1;
         ok[jj] = s >= 0 && (int64_t)s < a.recv_rows;
@@ -63,7 +68,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
         }
       }
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
+      for (int jj = 0; jj < kBatch; ++jj) {
         if (!ok[jj]) continue;
 #pragma unroll
         for (int u = 0; u < kVec; ++u)
@@ -90,16 +95,33 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   }
 }
 
-hipError_t launch_combine(const CombineArgs& a, hipStream_t s) {
-  if (a.tokens <= 0) return hipSuccess;
+// Eight choices a batch where few workgroups run: 48 tokens of 8 rows of 14 KiB 6.2 -> 4.1 us, 16 of 6
+// rows of 4 KiB 3.6 -> 3.5; with four or fewer choices, or many workgroups (4096 tokens of 6 rows of
+// 4 KiB 19.1 -> 20.2), the wider batch only costs registers.
+// It rides on the two-vector kernel, whose registers it fits, so the one-vector kernel keeps its own.
+template <int kVec>
+__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
+  if (kVec == 2 && a.few)
+    combine_rows<1, 8>(a);
+  else
+    combine_rows<kVec, 4>(a);
+}
+
+hipError_t launch_combine(const CombineArgs& args, hipStream_t s) {
+  if (args.tokens <= 0) return hipSuccess;
+  CombineArgs a = args;
   const int64_t nvec = a.H / 8;
-  const int vec = nvec <= 256 ? 1 : nvec <= 512 ? 2 : 4;
-  const int64_t spans = (nvec + 256 * vec - 1) / (256 * vec);
+  int vec = nvec <= 256 ? 1 : nvec <= 512 ? 2 : 4;
+  // With four or fewer choices one batch holds them, and the spread costs more than it gives
+  // (16 tokens of 2 rows of 8 KiB 2.85 -> 2.92 us).
+  a.few = a.k > 4 && a.tokens * ((nvec + 256 * vec - 1) / (256 * vec)) < kFewWorkgroups;
+  const int width = a.few ? 256 : 256 * vec;
+  const int64_t spans = (nvec + width - 1) / width;
   const int grid = (int)std::min<int64_t>(a.tokens * spans, 65536);
-  if (vec == 1)
-    hipLaunchKernelGGL(combine_kernel<1>, dim3(grid), dim3(256), 0, s, a);
-  else if (vec == 2)
+  if (a.few || vec == 2)
     hipLaunchKernelGGL(combine_kernel<2>, dim3(grid), dim3(256), 0, s, a);
+  else if (vec == 1)
+    hipLaunchKernelGGL(combine_kernel<1>, dim3(grid), dim3(256), 0, s, a);
   else
     hipLaunchKernelGGL(combine_kernel<4>, dim3(grid), dim3(256), 0, s, a);
   return hipGetLastError();
