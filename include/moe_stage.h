@@ -290,7 +290,8 @@ int moe_stage_run_serial_devplan(moe_stage_t h, const void* dispatched_x,
  * array of MOE_STATIC_SCRATCH_BYTES that the library holds on each GPU it runs on until the
  * process ends; the call allocates nothing: no hipMalloc, hipFree, stream, event or pinned host
  * memory.  It enqueues on `stream` (a hipStream_t; NULL = null stream) and returns; the two
- * receive-buffer tables go up with hipMemcpyAsync from the caller's host arrays.  Every call on
+ * receive-buffer tables travel in kernel arguments (more than 16 ranks: with hipMemcpyAsync from the
+ * caller's host arrays).  Every call on
  * a GPU shares that GPU's array and leaves its contents behind (each run's kernels reset what
  * must start at zero): calls that overlap on one GPU -- on different streams, or from different
  * threads -- race and must not be made.  Errors: MOE_ECAPACITY when the configuration's

@@ -134,7 +134,8 @@ struct moe_stage_s {
   bool last_overlapped = false;
   bool dev_hdr_pending = false;  // its header has not been read back yet
   int32_t dev_status = 0, dev_bad_row = 0;
-  uint8_t* h_stage[2] = {nullptr, nullptr};
+  uint8_t* h_stage[2] = {nullptr, nullptr};  // pinned, and as the device sees it:
+  void* h_stage_dev[2] = {nullptr, nullptr};
   hipEvent_t stage_free[2] = {nullptr, nullptr};
   int stage_idx = 0;
   uint32_t epoch = 0;
@@ -355,10 +356,13 @@ int prepare(moe_stage_s* h, bool overlapped, const void* x,
   memcpy(hs + lay->ret, ret, sizeof(void*) * (size_t)c.num_ranks);
   memcpy(hs + lay->ret + sizeof(void*) * (size_t)c.num_ranks, return_rows, sizeof(int64_t) * (size_t)c.num_ranks);
 
-  HIP_TRY(h, hipMemcpyAsync(h->d_plan, hs, lay->total, hipMemcpyHostToDevice, stream));
-  HIP_TRY(h, hipEventRecord(h->stage_free[si], stream));
   const uint32_t epoch = next_epoch(h);
-  HIP_TRY(h, launch_init(init_args(h, overlapped, false, (int32_t)P.tile_rows.size(), P.n_lrows(), epoch), stream));
+  InitArgs ia = init_args(h, overlapped, false, (int32_t)P.tile_rows.size(), P.n_lrows(), epoch);
+  ia.up_src = h->h_stage_dev[si];
+  ia.up_dst = h->d_plan;
+  ia.up_n16 = (int64_t)(lay->total / 16);  // every table starts and ends on 256 bytes
+  HIP_TRY(h, launch_init(ia, stream));
+  HIP_TRY(h, hipEventRecord(h->stage_free[si], stream));
   h->epoch = epoch;
   h->last_lay = *lay;
   h->last_dev = false;
@@ -397,7 +401,15 @@ int prepare_device(moe_stage_s* h, bool overlapped, const void* x, const int32_t
     return set_err(h, MOE_EUNSUPPORTED, "hidden or ffn too large for the work-item encoding");
   *lay = h->cap_lay;
   const size_t R = (size_t)c.num_ranks;
-  if (h->h_stage[0]) {
+  const uint32_t epoch = next_epoch(h);
+  InitArgs ia = init_args(h, overlapped, true, h->max_tile_rows, h->max_lrows, epoch);
+  if (R <= (size_t)kArgRanks) {  // the receive-buffer table goes along in the reset's arguments
+    ia.n_ret = c.num_ranks;
+    ia.ret_dst = (void**)(h->d_plan + lay->ret);
+    ia.ret_rows_dst = (int64_t*)(h->d_plan + lay->ret + sizeof(void*) * R);
+    memcpy(ia.ret, ret, sizeof(void*) * R);
+    memcpy(ia.ret_rows, return_rows, sizeof(int64_t) * R);
+  } else if (h->h_stage[0]) {
     const int si = h->stage_idx;
     h->stage_idx ^= 1;
     HIP_TRY(h, hipEventSynchronize(h->stage_free[si]));
@@ -445,9 +457,7 @@ int prepare_device(moe_stage_s* h, bool overlapped, const void* x, const int32_t
   a.groups = (Group*)(h->d_plan + lay->groups);
   a.tail_rows = (int32_t*)(h->d_plan + lay->tail);
   a.ws = h->ws;
-  const uint32_t epoch = next_epoch(h);
-  HIP_TRY(h, launch_devplan(a, init_args(h, overlapped, true, h->max_tile_rows, h->max_lrows, epoch), h->max_items,
-                            h->num_cus, stream));
+  HIP_TRY(h, launch_devplan(a, ia, h->max_items, h->num_cus, stream));
   h->epoch = epoch;
   h->last.plan_us =
       std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count();
@@ -758,8 +768,10 @@ int moe_stage_create(const moe_stage_config_t* cfg, moe_stage_t* out) {
       !try_hip(hipMemset(h->simd_waves, 0, sizeof(uint32_t) * kWaveCounters), "hipMemset(counters)") ||
       !try_hip(hipMalloc(&h->d_plan, h->plan_cap), "hipMalloc(plan)") ||
       !try_hip(hipMalloc(&h->dev_ws, ws_bytes), "hipMalloc(planner scratch)") ||
-      !try_hip(hipHostMalloc(&h->h_stage[0], h->plan_cap, hipHostMallocDefault), "hipHostMalloc") ||
-      !try_hip(hipHostMalloc(&h->h_stage[1], h->plan_cap, hipHostMallocDefault), "hipHostMalloc") ||
+      !try_hip(hipHostMalloc(&h->h_stage[0], h->plan_cap, hipHostMallocCoherent | hipHostMallocMapped), "hipHostMalloc") ||
+      !try_hip(hipHostMalloc(&h->h_stage[1], h->plan_cap, hipHostMallocCoherent | hipHostMallocMapped), "hipHostMalloc") ||
+      !try_hip(hipHostGetDevicePointer(&h->h_stage_dev[0], h->h_stage[0], 0), "hipHostGetDevicePointer") ||
+      !try_hip(hipHostGetDevicePointer(&h->h_stage_dev[1], h->h_stage[1], 0), "hipHostGetDevicePointer") ||
       !try_hip(hipMemset(h->hws, 0, hws_bytes), "hipMemset(hws)") ||
       !try_hip(hipMemset(h->y, 0, y_bytes), "hipMemset(y)") ||
       !try_hip(hipMemset(h->flags, 0, flag_bytes), "hipMemset(flags)") ||

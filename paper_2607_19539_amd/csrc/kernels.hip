@@ -22,6 +22,7 @@
 #include <limits.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "init_device.hpp"
@@ -1582,7 +1583,7 @@ __global__ __launch_bounds__(256) void init_kernel(InitArgs a) {
 }
 
 hipError_t launch_init(const InitArgs& a, hipStream_t s) {
-  int grid = 64;
+  int grid = (int)std::min<int64_t>(1024, std::max<int64_t>(64, a.up_n16 / 256));
   if (a.poison || a.n_fill_ones > (1 << 18)) grid = 1024;
   hipLaunchKernelGGL(init_kernel, dim3(grid), dim3(256), 0, s, a);
   return hipGetLastError();

@@ -127,6 +127,9 @@ struct ScatterArgs {
   uint32_t* wcount;        // MOE_WRITE_COUNTS: [logical rows] 8-byte words stored into receive buffers
 };
 
+// Ranks whose receive-buffer table travels in a kernel's arguments instead of a copy of its own.
+constexpr int kArgRanks = 16;
+
 struct InitArgs {
   RunCounters* ctr;
   uint16_t* poison;        // optional: filled with bf16 NaN
@@ -143,6 +146,16 @@ struct InitArgs {
   uint32_t* fill_ones;     // optional: words to set to all-ones bits (device planner scratch)
   int64_t n_fill_ones;
   PlanHeader* plan_hdr;    // optional: header the device planner fills; reset to no error
+  // Optional: a host-built plan, read by this kernel straight from pinned host memory.
+  const void* up_src;
+  void* up_dst;
+  int64_t up_n16;          // 16-byte vectors
+  // Optional: the receive-buffer table by value (at most kArgRanks ranks): pointers, then row counts.
+  int32_t n_ret;
+  void** ret_dst;
+  int64_t* ret_rows_dst;
+  void* ret[kArgRanks];
+  int64_t ret_rows[kArgRanks];
 };
 
 

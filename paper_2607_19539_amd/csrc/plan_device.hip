@@ -686,7 +686,7 @@ __global__ __launch_bounds__(kWg) void planner_small_kernel(DevPlanArgs a, InitA
   for (int i = tid; i < E_l * R; i += kWg) run_lo[i] = -1;
   if (tid == 0) s_code = s_pad = s_remote = 0, s_bad = INT_MAX;
   if (tid <= E_l) off[tid] = a.off[tid];
-  for (int r = tid; r < R; r += kWg) rrows[r] = a.return_rows[r];
+  for (int r = tid; r < R; r += kWg) rrows[r] = ia.n_ret ? ia.ret_rows[r] : a.return_rows[r];
   lds_barrier();
   const int32_t rows = off[E_l];
   if (tid < E_l && off[tid] > off[tid + 1]) s_code = MOE_EROUTING;

@@ -19,7 +19,7 @@ def case(E_l, R, rows, contiguous, seed, me=0):
 
 @pytest.mark.parametrize("E_l,R,rows,contiguous", [
     (1, 1, 1, True), (1, 3, 2048, False), (2, 4, 255, True), (64, 16, 2048, True), (64, 16, 2047, False),
-    (63, 5, 700, False), (8, 2, 2048, True),
+    (63, 5, 700, False), (8, 2, 2048, True), (2, 40, 300, True),   # 40 ranks: past the table in arguments
 ])
 def test_both_sides_of_the_row_limit(E_l, R, rows, contiguous):
     c = case(E_l, R, rows, contiguous, seed=E_l + R + rows, me=R - 1)
