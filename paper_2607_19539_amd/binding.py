@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import atexit
 import ctypes
+import functools
 import os
 import sys
 from typing import Dict, Optional, Sequence
@@ -158,6 +159,9 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     return lib
 
 
+_I32, _I64 = np.dtype(np.int32), np.dtype(np.int64)
+
+
 class MoeError(RuntimeError):
     def __init__(self, code: int, msg: str):
         super().__init__(f"{ERROR_NAMES.get(code, code)}: {msg}")
@@ -165,19 +169,23 @@ class MoeError(RuntimeError):
 
 
 def _host_i32(a) -> np.ndarray:
+    if type(a) is np.ndarray and a.dtype == _I32 and a.flags.c_contiguous:
+        return a
     if hasattr(a, "detach"):
         a = a.detach().cpu().numpy()
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
 def _host_i64(a) -> np.ndarray:
+    if type(a) is np.ndarray and a.dtype == _I64 and a.flags.c_contiguous:
+        return a
     if hasattr(a, "detach"):
         a = a.detach().cpu().numpy()
     return np.ascontiguousarray(a, dtype=np.int64)
 
 
-def _np_ptr(a: np.ndarray):
-    return a.ctypes.data_as(ctypes.c_void_p)
+def _np_ptr(a: np.ndarray) -> int:
+    return a.__array_interface__["data"][0]
 
 
 def _dev_ptr(t) -> int:
@@ -225,6 +233,15 @@ def _shape(t):
     return tuple(int(d) for d in t.shape), int(esize)
 
 
+def _is(t, want) -> bool:
+    """True for a tensor or array of exactly this shape with 2-byte elements (the usual case, told
+    without taking the shape apart)."""
+    try:
+        return t.shape == want and t.dtype.itemsize == 2
+    except AttributeError:
+        return False
+
+
 def validate_run_args(cfg, x, rows, n_routing, w1, w3, w2, return_bufs, return_rows):
     """Checks that every buffer is as large as the call says, before anything reaches the library
     (whose kernels would otherwise read or write past a short buffer).  ``rows`` is the routed-row
@@ -241,11 +258,13 @@ def validate_run_args(cfg, x, rows, n_routing, w1, w3, w2, return_bufs, return_r
         raise ValueError(f"row_src_rank and row_slot must have expert_offsets[-1] = {rows} entries, not {n_src}")
     n_rows = n_src if rows is None else max(rows, 0)
     for name, t, want in (("w1", w1, (E, F, H)), ("w3", w3, (E, F, H)), ("w2", w2, (E, H, F))):
+        if _is(t, want):
+            continue
         sh = _shape(t)
         if sh is not None and (sh[0] != want or sh[1] != 2):
             raise ValueError(f"{name} must be [{', '.join(map(str, want))}] with 2-byte elements, got {sh[0]} "
                              f"of {sh[1]}-byte elements")
-    sh = _shape(x)
+    sh = None if _is(x, (n_rows, H)) else _shape(x)
     if sh is not None and (len(sh[0]) != 2 or sh[0][1] != H or sh[0][0] < n_rows or sh[1] != 2):
         raise ValueError(f"dispatched_x must be [>= {n_rows}, {H}] with 2-byte elements, got {sh[0]} of "
                          f"{sh[1]}-byte elements")
@@ -254,6 +273,8 @@ def validate_run_args(cfg, x, rows, n_routing, w1, w3, w2, return_bufs, return_r
     if len(return_rows) != R:
         raise ValueError(f"return_rows must hold num_ranks = {R} entries, not {len(return_rows)}")
     for r, (b, n) in enumerate(zip(return_bufs, return_rows)):
+        if _is(b, (n, H)):
+            continue
         sh = _shape(b)
         if sh is not None and (len(sh[0]) != 2 or sh[0][1] != H or sh[0][0] < int(n) or sh[1] != 2):
             raise ValueError(f"return_bufs[{r}] must be [>= return_rows[{r}] = {int(n)}, {H}] with 2-byte "
@@ -267,24 +288,31 @@ def _cfg_of(h) -> moe_stage_config_t:
     return cfg
 
 
+@functools.lru_cache(maxsize=64)
+def _ptr_array(n: int):
+    """The ctypes type of n pointers (making one anew costs some microseconds)."""
+    return ctypes.c_void_p * n
+
+
 def _run_args(x, expert_offsets, row_src_rank, row_slot, w1, w3, w2, return_bufs, return_rows, cfg=None):
     off, src, slot = _host_i32(expert_offsets), _host_i32(row_src_rank), _host_i32(row_slot)
     rr = _host_i64(return_rows if return_rows is not None else [b.shape[0] for b in return_bufs])
     if cfg is not None:
         validate_run_args(cfg, x, int(off[-1]) if off.size else None, (off.size, src.size, slot.size),
                           w1, w3, w2, return_bufs, rr)
-    ptrs = (ctypes.c_void_p * len(return_bufs))(*[_dev_ptr(b) for b in return_bufs])
+    ptrs = _ptr_array(len(return_bufs))(*[_dev_ptr(b) for b in return_bufs])
     keep = (off, src, slot, rr, ptrs)
     args = [_dev_ptr(x) if x is not None else None, _np_ptr(off), _np_ptr(src), _np_ptr(slot),
             _dev_ptr(w1) if w1 is not None else None, _dev_ptr(w3) if w3 is not None else None,
-            _dev_ptr(w2) if w2 is not None else None, ctypes.cast(ptrs, ctypes.c_void_p), _np_ptr(rr)]
+            _dev_ptr(w2) if w2 is not None else None, ctypes.addressof(ptrs), _np_ptr(rr)]
     return args, keep
 
 
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # the handle without a Stream object
+        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -318,10 +346,10 @@ def _run_args_dev(x, expert_offsets, row_src_rank, row_slot, w1, w3, w2, return_
         # The routed-row count lives on the device; the routing arrays' own lengths bound it.
         validate_run_args(cfg, x, None, (expert_offsets.numel(), row_src_rank.numel(), row_slot.numel()),
                           w1, w3, w2, return_bufs, rr)
-    ptrs = (ctypes.c_void_p * len(return_bufs))(*[_dev_ptr(b) for b in return_bufs])
+    ptrs = _ptr_array(len(return_bufs))(*[_dev_ptr(b) for b in return_bufs])
     keep = (rr, ptrs)
     args = [_dev_ptr(x), _dev_ptr(expert_offsets), _dev_ptr(row_src_rank), _dev_ptr(row_slot),
-            _dev_ptr(w1), _dev_ptr(w3), _dev_ptr(w2), ctypes.cast(ptrs, ctypes.c_void_p), _np_ptr(rr)]
+            _dev_ptr(w1), _dev_ptr(w3), _dev_ptr(w2), ctypes.addressof(ptrs), _np_ptr(rr)]
     return args, keep
 
 
@@ -361,7 +389,7 @@ def moe_combine(recv, slot, gate, out, bad_slots=None, stream=None) -> int:
     ``recv`` [recv_rows, H] and ``out`` [T, H] are 2-byte device tensors (bf16 bits),
     ``slot`` [T, k] int32 and ``gate`` [T, k] float32 device tensors, ``bad_slots`` an
     optional one-element int32/uint32 device tensor that counts out-of-range slots."""
-    if recv.dim() != 2 or out.dim() != 2 or slot.dim() != 2 or gate.shape != slot.shape:
+    if len(recv.shape) != 2 or len(out.shape) != 2 or len(slot.shape) != 2 or gate.shape != slot.shape:
         raise ValueError("recv [rows, H], out [T, H], slot and gate [T, k] expected")
     if recv.element_size() != 2 or out.element_size() != 2:
         raise ValueError("recv and out must hold 2-byte elements (bf16 bits)")
@@ -369,11 +397,12 @@ def moe_combine(recv, slot, gate, out, bad_slots=None, stream=None) -> int:
     if slot.dtype != torch.int32 or gate.dtype != torch.float32:
         raise ValueError("slot must be int32 and gate float32")
     T, k = slot.shape
-    if out.shape[0] != T or out.shape[1] != recv.shape[1]:
+    rows, H = recv.shape
+    if out.shape != (T, H):
         raise ValueError("out must be [T, H] with the receive buffer's H")
     bad = None if bad_slots is None else _dev_ptr(bad_slots)
-    rc = load().moe_combine(_dev_ptr(recv), int(recv.shape[0]), int(recv.shape[1]), _dev_ptr(slot),
-                            _dev_ptr(gate), int(T), int(k), _dev_ptr(out), bad, _stream_ptr(stream))
+    rc = load().moe_combine(_dev_ptr(recv), rows, H, _dev_ptr(slot), _dev_ptr(gate), T, k, _dev_ptr(out), bad,
+                            _stream_ptr(stream))
     return _check(rc)
 
 
