@@ -134,7 +134,8 @@ struct moe_stage_s {
   bool last_overlapped = false;
   bool dev_hdr_pending = false;  // its header has not been read back yet
   int32_t dev_status = 0, dev_bad_row = 0;
-  uint8_t* h_stage[2] = {nullptr, nullptr};  // pinned, and as the device sees it:
+  uint8_t* h_pinned = nullptr;               // one pinned allocation: both staging halves, the stamps
+  uint8_t* h_stage[2] = {nullptr, nullptr};  // the staging halves, and as the device sees them:
   void* h_stage_dev[2] = {nullptr, nullptr};
   hipEvent_t stage_free[2] = {nullptr, nullptr};
   int stage_idx = 0;
@@ -768,10 +769,10 @@ int moe_stage_create(const moe_stage_config_t* cfg, moe_stage_t* out) {
       !try_hip(hipMemset(h->simd_waves, 0, sizeof(uint32_t) * kWaveCounters), "hipMemset(counters)") ||
       !try_hip(hipMalloc(&h->d_plan, h->plan_cap), "hipMalloc(plan)") ||
       !try_hip(hipMalloc(&h->dev_ws, ws_bytes), "hipMalloc(planner scratch)") ||
-      !try_hip(hipHostMalloc(&h->h_stage[0], h->plan_cap, hipHostMallocCoherent | hipHostMallocMapped), "hipHostMalloc") ||
-      !try_hip(hipHostMalloc(&h->h_stage[1], h->plan_cap, hipHostMallocCoherent | hipHostMallocMapped), "hipHostMalloc") ||
-      !try_hip(hipHostGetDevicePointer(&h->h_stage_dev[0], h->h_stage[0], 0), "hipHostGetDevicePointer") ||
-      !try_hip(hipHostGetDevicePointer(&h->h_stage_dev[1], h->h_stage[1], 0), "hipHostGetDevicePointer") ||
+      !try_hip(hipHostMalloc((void**)&h->h_pinned, 2 * h->plan_cap + 2 * kAutoRing * sizeof(uint64_t),
+                             hipHostMallocCoherent | hipHostMallocMapped),
+               "hipHostMalloc") ||
+      !try_hip(hipHostGetDevicePointer(&h->h_stage_dev[0], h->h_pinned, 0), "hipHostGetDevicePointer") ||
       !try_hip(hipMemset(h->hws, 0, hws_bytes), "hipMemset(hws)") ||
       !try_hip(hipMemset(h->y, 0, y_bytes), "hipMemset(y)") ||
       !try_hip(hipMemset(h->flags, 0, flag_bytes), "hipMemset(flags)") ||
@@ -810,10 +811,10 @@ int moe_stage_create(const moe_stage_config_t* cfg, moe_stage_t* out) {
     return bail(MOE_EHIP);
   for (auto& ev : h->autos.done)
     if (!try_hip(hipEventCreateWithFlags(&ev, kSyncEv), "hipEventCreate")) return bail(MOE_EHIP);
-  if (!try_hip(hipHostMalloc((void**)&h->autos.stamps, 2 * kAutoRing * sizeof(uint64_t),
-                             hipHostMallocCoherent | hipHostMallocMapped),
-               "hipHostMalloc"))
-    return bail(MOE_EHIP);
+  h->h_stage[0] = h->h_pinned;
+  h->h_stage[1] = h->h_pinned + h->plan_cap;
+  h->h_stage_dev[1] = (uint8_t*)h->h_stage_dev[0] + h->plan_cap;
+  h->autos.stamps = (uint64_t*)(h->h_pinned + 2 * h->plan_cap);  // plan_cap is a multiple of 256
   if (h->cfg.flags & MOE_KERNEL_TIMING) {
     h->ring.resize(kTimingRing);
     for (auto& r : h->ring)
@@ -1324,7 +1325,6 @@ int moe_stage_destroy(moe_stage_t h) {
     if (ev) (void)hipEventDestroy(ev);
   for (hipEvent_t ev : h->autos.done)
     if (ev) (void)hipEventDestroy(ev);
-  if (h->autos.stamps) (void)hipHostFree(h->autos.stamps);
   for (const auto& q : h->queues) {
     (void)hipStreamDestroy(q.cons);
     if (q.prod) (void)hipStreamDestroy(q.prod);
@@ -1334,8 +1334,7 @@ int moe_stage_destroy(moe_stage_t h) {
                   (void*)h->partials, (void*)h->arrivals, h->dev_ws, (void*)h->wg_rec, (void*)h->copy_rec,
                   (void*)h->tile_ready, (void*)h->simd_waves, (void*)h->abandoned, (void*)h->wcount})
     if (p) (void)hipFree(p);
-  for (uint8_t* p : h->h_stage)
-    if (p) (void)hipHostFree(p);
+  if (h->h_pinned) (void)hipHostFree(h->h_pinned);
   delete h;
   return MOE_OK;
 }

@@ -197,7 +197,7 @@ int producer_blocks_per_cu();
 constexpr int kProducerThreads = 256;
 constexpr int kConsumerThreads = 256;
 // 16-byte vectors per consumer lane and copy chunk (two chunks in flight): beside the producer,
-// within 56 VGPRs (two such waves and a producer wave of 136 VGPRs + 256 AGPRs fill a SIMD's
+// within 56 VGPRs (two such waves and a producer wave of at most 144 VGPRs + 256 AGPRs fill a SIMD's
 // 512 registers); on compute units of its own, within 128.
 constexpr int kCopyUnroll = 3;
 constexpr int kCopyUnrollOwn = 10;
@@ -220,7 +220,7 @@ constexpr int kPollSleep = 4;
 constexpr uint32_t kPollBackoffMax = 16;
 constexpr int kTailGrid = 1024; // tail kernel workgroups (one pass each on the usual tail)
 // Consumer waves per SIMD the register budget must allow: at most 512 / 8 = 64 VGPRs each (the
-// copy chunk keeps the kernel at 56, so two waves fit beside a producer wave of 392 registers).
+// copy chunk keeps the kernel at 56, so two waves fit beside a producer wave of up to 400 registers).
 constexpr int kConsumerMinWaves = 8;
 // Consumer waves beside the producer in all (their copy rate is latency-bound per wave; about 256
 // waves saturate it), spread over however many compute units the split gives the consumer.
