@@ -167,7 +167,6 @@ struct CombineArgs {
   uint32_t* bad_slots;     // optional: incremented once per out-of-range slot
   int64_t recv_rows, tokens;
   int32_t k, H;
-  int32_t few;             // set by launch_combine: few workgroups, many choices
 };
 
 hipError_t launch_init(const InitArgs& a, hipStream_t s);

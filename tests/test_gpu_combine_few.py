@@ -1,8 +1,8 @@
 """The combine where few workgroups run, on either side of that line: bit-exact with the oracle's order.
 
-Eight choices in a batch and one vector per thread (more than four choices, under 512 workgroups), next
-to the wider split: ragged hidden sizes around one and two spans, choices around the batch, slots out of
-range."""
+One vector per thread (up to 256 workgroups of the wider split, 512 with eight choices or more), next
+to the wider split: ragged hidden sizes around one and two parts of a row, choices around the batches of
+four, slots out of range."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,10 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("H,T,k", [(8, 1, 5), (2048, 3, 8), (2056, 5, 9), (4096, 255, 5), (4104, 7, 17), (7168, 48, 8),
-                                   (2048, 511, 6), (2048, 512, 6), (7168, 512, 8), (4096, 16, 4)])
+                                   (2048, 511, 6), (2048, 512, 6), (7168, 512, 8), (4096, 16, 4),
+                                   # either side of the lines of the split: tokens, choices, a short last part
+                                   (2056, 256, 6), (2056, 257, 6), (2056, 257, 8), (7168, 256, 5), (7168, 257, 5),
+                                   (7168, 513, 8), (16384, 129, 6), (64, 100, 9), (65536, 3, 3), (8, 70000, 2)])
 def test_few_workgroups(H, T, k):
     g = np.random.default_rng(H + T + k)
     rows = T * k + 3

@@ -5,6 +5,7 @@ A producer wave holds 256 accumulation registers plus its vector registers; in a
 run two consumer waves must fit beside it on each SIMD (512 registers), and no kernel may
 spill to scratch (a spill in the MFMA loop costs an order of magnitude).
 """
+import ctypes
 import os
 import re
 import subprocess
@@ -30,11 +31,14 @@ def kernels(tmp_path_factory):
                         "-S", os.path.join(CSRC, src), f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}", "-o", str(out),
                         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"],
                        check=True, capture_output=True)
-        meta = out.read_text().split("amdhsa.kernels:", 1)[1]
+        out_text = out.read_text()
+        meta = out_text.split("amdhsa.kernels:", 1)[1]
         for block in re.split(r"\n  - ", meta)[1:]:
             fields = dict(re.findall(r"^\s*\.(\w+):\s+(\S+)", block, re.M))
             if "name" in fields:
                 found[fields["name"]] = fields
+                body = out_text.split("\n" + fields["name"] + ":", 1)[1].split(".Lfunc_end", 1)[0]
+                found[fields["name"]]["body"] = body
     return found
 
 
@@ -77,6 +81,44 @@ def test_every_split_variant_is_instantiated(kernels):
 def test_combine_variants_present(kernels):
     names = set(by_name(kernels, "combine_kernel"))
     assert len(names) == 3, names
+
+
+def test_combine_rows_of_a_batch_are_in_flight_together(kernels):
+    """The combine's time with few tokens is a chain of loads: between the row loads of a batch of four
+    choices nothing may wait for a vector load (three choices' loads in a row here: the compiler may lay
+    the last one's out elsewhere)."""
+    for name, f in by_name(kernels, "combine_kernel").items():
+        vec = int(re.search(r"combine_kernelILi(\d)E", name).group(1))
+        ops = re.findall(r"^\s(global_load_dwordx4|s_waitcnt vmcnt\(\d+\))", f["body"], re.M)
+        longest = run = 0
+        for op in ops:
+            run = run + 1 if op.startswith("global_load") else 0
+            longest = max(longest, run)
+        assert longest >= 3 * vec, (name, ops)
+
+
+@pytest.mark.parametrize("H,T,k,vec", [
+    # A vector per thread as long as the longer ones leave compute units idle.
+    (7168, 48, 8, 1), (7168, 256, 2, 1), (4096, 256, 6, 1), (7168, 512, 8, 1), (16384, 128, 5, 1), (8, 1, 1, 1),
+    # Past that; a row with a nearly empty second part was spread up to 511 tokens before, 1.3 times slower.
+    (2056, 257, 6, 2), (2056, 257, 8, 2), (4096, 4096, 2, 2), (7168, 257, 7, 4), (7168, 513, 9, 4), (16384, 129, 5, 4),
+    # Rows of one vector per thread are never split further.
+    (2048, 1, 8, 1), (2048, 8192, 8, 1),
+])
+def test_combine_split_at_its_lines(combine_vec, H, T, k, vec):
+    assert combine_vec(T, k, H) == vec
+
+
+@pytest.fixture(scope="module")
+def combine_vec(tmp_path_factory):
+    d = tmp_path_factory.mktemp("split")
+    (d / "split.cpp").write_text('#include "combine_split.hpp"\n'
+                                 'extern "C" int f(long T, int k, int H) { return moe::combine_vec(T, k, H); }\n')
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", f"-I{CSRC}", str(d / "split.cpp"), "-o",
+                    str(d / "split.so")], check=True, capture_output=True)
+    fn = ctypes.CDLL(str(d / "split.so")).f
+    fn.argtypes = [ctypes.c_long, ctypes.c_int, ctypes.c_int]
+    return fn
 
 
 def test_consumer_leaves_lds_to_the_producer(kernels):
