@@ -169,7 +169,7 @@ class MoeError(RuntimeError):
 
 
 def _host_i32(a) -> np.ndarray:
-    if type(a) is np.ndarray and a.dtype == _I32 and a.flags.c_contiguous:
+    if type(a) is np.ndarray and a.dtype == _I32 and a.ndim and a.flags.c_contiguous:
         return a
     if hasattr(a, "detach"):
         a = a.detach().cpu().numpy()
@@ -177,7 +177,7 @@ def _host_i32(a) -> np.ndarray:
 
 
 def _host_i64(a) -> np.ndarray:
-    if type(a) is np.ndarray and a.dtype == _I64 and a.flags.c_contiguous:
+    if type(a) is np.ndarray and a.dtype == _I64 and a.ndim and a.flags.c_contiguous:
         return a
     if hasattr(a, "detach"):
         a = a.detach().cpu().numpy()

@@ -188,6 +188,23 @@ def test_binding_checks_buffer_shapes_before_the_library(case):
             B.validate_run_args(*args)
 
 
+def test_scalar_host_arrays_are_taken_as_one_entry():
+    """One rank's row count as a number, a numpy scalar or an array of no dimensions: one entry, of the
+    library's type; arrays that already are what the library reads are passed on as they are."""
+    for host, own, other in ((B._host_i64, np.int64, np.int32), (B._host_i32, np.int32, np.int64)):
+        for value in (7, own(7), other(7), np.array(7, own), np.array(7, other)):
+            got = host(value)
+            assert got.shape == (1,) and got.dtype == own and got[0] == 7
+        a = np.arange(6, dtype=own)
+        assert host(a) is a
+        assert host(a[::2]).flags.c_contiguous and host(a[::2]).tolist() == [0, 2, 4]
+        assert host(a.astype(a.dtype.newbyteorder())).tolist() == a.tolist()
+    torch = pytest.importorskip("torch")
+    cfg = B.make_config(256, 512, 2, 1, 0, 64)
+    B.validate_run_args(cfg, _meta(torch, 5, 256), 5, (3, 5, 5), _meta(torch, 2, 512, 256), _meta(torch, 2, 512, 256),
+                        _meta(torch, 2, 256, 512), [_meta(torch, 8, 256)], B._host_i64(np.array(8)))
+
+
 def test_run_wrappers_refuse_a_handle_they_did_not_create():
     with pytest.raises(ValueError):
         B.moe_stage_run(12345, None, [0, 0, 0], [], [], None, None, None, [], None)
