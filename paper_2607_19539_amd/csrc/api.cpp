@@ -889,7 +889,6 @@ static int run_overlapped(moe_stage_t h, bool dev, const void* x, const int32_t*
   h->last.consumer_cus = c_eff;
   uint32_t mode = (h->cfg.flags & MOE_TEST_NO_SIGNAL) ? 0u : kModeSignal;
   if (h->cfg.flags & MOE_LOCAL_DIRECT) mode |= kModeLocalDirect;
-  if (h->cfg.down_split_k == 0) mode |= kModeDeferTail;
   ProducerArgs pgu = producer_args(h, lay, x, w1, w3, w2, mode, false);
   const ProducerArgs pdn = producer_args(h, lay, x, w1, w3, w2, mode, true);
   ConsumerArgs ca{};
@@ -979,7 +978,7 @@ static int run_overlapped(moe_stage_t h, bool dev, const void* x, const int32_t*
   if (!on_caller && (rc = gate_up()) != MOE_OK) return rc;
   if (tr) HIP_TRY(h, hipEventRecord(tr->ev[6], ps));
   if (producer && (!known || h->plan.n_down > 0)) HIP_TRY(h, launch_producer(pdn, true, pgrid, ps));
-  if (producer && (pdn.mode & kModeDeferTail) && (!known || h->plan.n_split_rows > 0))
+  if (producer && pdn.split_k == 0 && (!known || h->plan.n_split_rows > 0))
     HIP_TRY(h, launch_tail(tail_args(h, lay, pdn), kTailGrid, ps));
   if (tr) HIP_TRY(h, hipEventRecord(tr->ev[2], ps));
   if (drain) {
@@ -1034,7 +1033,7 @@ static int run_serial(moe_stage_t h, bool dev, const void* x, const int32_t* off
   h->last.auto_cu_split = -1;
   h->last.consumer_cus = 0;
   const bool direct_all = (h->cfg.flags & MOE_DIRECT_ALL) != 0;
-  const uint32_t mode = (direct_all ? kModeDirectAll : 0u) | (h->cfg.down_split_k == 0 ? kModeDeferTail : 0u);
+  const uint32_t mode = direct_all ? kModeDirectAll : 0u;
   const ProducerArgs pgu = producer_args(h, lay, x, w1, w3, w2, mode, false);
   const ProducerArgs pa = producer_args(h, lay, x, w1, w3, w2, mode, true);
   if (tr) HIP_TRY(h, hipEventRecord(tr->ev[1], stream));
@@ -1044,7 +1043,7 @@ static int run_serial(moe_stage_t h, bool dev, const void* x, const int32_t* off
   if (!known || h->plan.n_down > 0) HIP_TRY(h, launch_producer(pa, true, pgrid, stream));
   // Split tail tiles: the return copy adds their parts straight into the rows' slots; without one
   // (direct_all) a tail launch does.
-  const bool tail = (pa.mode & kModeDeferTail) && (!known || h->plan.n_split_rows > 0);
+  const bool tail = pa.split_k == 0 && (!known || h->plan.n_split_rows > 0);
   if (tail && direct_all) HIP_TRY(h, launch_tail(tail_args(h, lay, pa), kTailGrid, stream));
   if (tr) HIP_TRY(h, hipEventRecord(tr->ev[2], stream));
   ScatterArgs sa{};

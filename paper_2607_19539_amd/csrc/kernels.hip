@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(kProducerThreads, 1) void producer_kernel(ProducerA
 }
 
 // ---------------------------------------------------------------------------
-// Tail: the split tile rows of a kModeDeferTail down launch.  Their parts only stored fp32
+// Tail: the split tile rows of a down launch with split_k 0.  Their parts only stored fp32
 // partials; here each workgroup pass takes four adjacent 16x16 blocks of a tile (one per wave:
 // 16 rows x 64 columns), issues the loads of all their parts at once, adds them in part order from
 // part 0, and stores those outputs where the down epilogue would (Y at device scope, or the local

@@ -11,8 +11,6 @@ namespace moe {
 constexpr uint32_t kModeSignal = 1u;       // raise a ready flag per down tile of a transfer tile row
 constexpr uint32_t kModeLocalDirect = 2u;  // local rows go straight to the local receive buffer
 constexpr uint32_t kModeDirectAll = 4u;    // every row goes straight to its receive buffer
-constexpr uint32_t kModeDeferTail = 8u;    // split tail tiles: parts only store their partials; the
-                                           // tail kernel after the launch adds them and writes the tiles
 
 // Timestamped runs: one record per producer workgroup of each launch (where it ran, how many
 // items it took, when it started and ended; 100 MHz wall clock) and one per consumer copy unit.
@@ -60,7 +58,8 @@ struct ProducerArgs {
   int32_t H, F, self_rank, down_per_row;
   uint32_t mode;
   int32_t compact;         // 1: a tile row's routed rows come first (no band padding between groups)
-  int32_t split_k;         // K parts of every down tile; 0 = per tile row (TileRow::split)
+  int32_t split_k;         // K parts of every down tile; 0 = per tile row (TileRow::split), whose parts
+                           // a following tail or scatter launch adds
   float* partials;         // fp32 part tiles (256 threads x 256) from TileRow::part_base on
   uint32_t* arrivals;      // [tiles] parts finished this run (zeroed by the init kernel)
   WgRecord* wg_rec;        // timestamped runs: [grid] records of this launch, else null
@@ -185,7 +184,8 @@ hipError_t launch_go(RunCounters* ctr, uint32_t epoch, hipStream_t s);
 // Measurement aid: a flat grid-stride copy of plain_n16 vectors from the staged output into the
 // first receive buffer (no flags, no copy units).
 hipError_t launch_plain_copy(const ConsumerArgs& a, int grid, hipStream_t s);
-// Split tail tiles of a kModeDeferTail down launch: one accumulator block of one tile per pass.
+// Split tail tiles of a down launch with split_k 0, which only stores their parts: a tail or a scatter
+// launch always has to follow it.  Four adjacent 16x16 blocks of one tile per pass.
 hipError_t launch_tail(const TailArgs& a, int grid, hipStream_t s);
 // Every routed row to its slot; with tail.tail_rows, those of split tail tiles from their parts.
 hipError_t launch_scatter(const ScatterArgs& a, const TailArgs& tail, int grid, hipStream_t s);
