@@ -662,7 +662,7 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-__global__ __launch_bounds__(kWg) void planner_small_kernel(DevPlanArgs a, InitArgs ia) {
+__global__ __launch_bounds__(kWg) void plan_small_kernel(DevPlanArgs a, InitArgs ia) {
   __shared__ unsigned long long seen[kSmallSeen];
   __shared__ int32_t src[kSmallRows], slot[kSmallRows + 1], off[kSmallExperts + 1];
   __shared__ int64_t rrows[kSmallGroups];
@@ -1111,7 +1111,7 @@ hipError_t launch_devplan(const DevPlanArgs& a, const InitArgs& init, int64_t ma
       if (e != hipSuccess) return e;
       ia.ctr = nullptr;
     }
-    hipLaunchKernelGGL(planner_small_kernel, dim3(1), dim3(kWg), 0, s, a, ia);
+    hipLaunchKernelGGL(plan_small_kernel, dim3(1), dim3(kWg), 0, s, a, ia);
     return hipGetLastError();
   }
   const hipError_t e = launch_init(init, s);

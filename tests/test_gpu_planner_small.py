@@ -5,7 +5,8 @@ import numpy as np
 import pytest
 
 from paper_2607_19539_amd import binding as B
-from tests.test_gpu_devplan import Case, _expect_device_error, check_both_paths, dispatch_routing
+from tests.test_gpu_devplan import (Case, _expect_device_error, assert_same_plan, check_both_paths, dispatch_routing,
+                                    host_tables)
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -25,13 +26,13 @@ def test_both_sides_of_the_row_limit(E_l, R, rows, contiguous):
     c = case(E_l, R, rows, contiguous, seed=E_l + R + rows, me=R - 1)
     for max_rows in (2048, 2049):
         for band_rows, mgb in ((0, 1), (16, 3)):
-            check_both_paths(c, overlapped=True, max_rows=max_rows, band_rows=band_rows, mgb=mgb, compare_outputs=False)
+            check_both_paths(c, overlapped=True, max_rows=max_rows, band_rows=band_rows, mgb=mgb)
         check_both_paths(c, overlapped=False, max_rows=max_rows)
 
 
 @pytest.mark.parametrize("E_l,R", [(65, 2), (64, 17)])
 def test_past_the_expert_and_pair_limits(E_l, R):
-    check_both_paths(case(E_l, R, 600, True, seed=E_l), overlapped=True, compare_outputs=False)
+    check_both_paths(case(E_l, R, 600, True, seed=E_l), overlapped=True)
 
 
 @pytest.mark.parametrize("max_rows", [2048, 2049])
@@ -53,6 +54,16 @@ def test_errors_on_both_sides(max_rows):
         i, j = 0, next(j for j in range(int(good.off[1]), 900) if good.src[j] == good.src[0])
         slot = good.slot.copy(); slot[j] = slot[i]   # the same (rank, slot) in two experts
         _expect_device_error(st, variant(slot=slot), B.MOE_EROUTING)
-        check = st.run_devplan(*good.dev_args(), cu_split=8)
-        assert check == B.MOE_OK if check is not None else True
-        st.query()
+        # A good call right after: the header and every table again, and the host-planned run's bytes.
+        for overlapped in (False, True):
+            good.fill()
+            (st.run_devplan if overlapped else st.run_serial_devplan)(*good.dev_args())
+            dev_out = good.out()
+            st.query()
+            assert_same_plan(st.plan(), host_tables(st, good, overlapped), f"overlapped={overlapped}")
+            good.fill()
+            (st.run if overlapped else st.run_serial)(*good.host_args())
+            for r, (a, b) in enumerate(zip(dev_out, good.out())):
+                assert np.array_equal(a, b), f"rank {r}, overlapped={overlapped}"
+            st.query()
+            _expect_device_error(st, variant(src=src), B.MOE_EROUTING, serial=not overlapped)

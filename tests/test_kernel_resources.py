@@ -139,11 +139,11 @@ def test_tail_kernel_fits_beside_the_polling_consumer(kernels):
 
 
 def test_device_planner_kernels_present_and_small(kernels):
-    """The four planner kernels: single-workgroup ones stay within the 160 KiB of LDS a workgroup
+    """The planner kernels, the four phases and the one for small plans: single-workgroup ones stay within the 160 KiB of LDS a workgroup
     may hold on gfx950, grid ones use little."""
     names = {n.split("_kernel")[0].rsplit("plan_", 1)[1]: f for n, f in by_name(kernels, "plan_").items()
              if "_kernel" in n}
-    assert set(names) == {"rows", "layout", "fill", "segs"}, names
+    assert set(names) == {"rows", "layout", "fill", "segs", "small"}, names
     for part, f in names.items():
         lds = int(f["group_segment_fixed_size"])
         assert lds <= 160 * 1024, (part, lds)
