@@ -464,7 +464,10 @@ __device__ __forceinline__ void narrow_mma(uint8_t* __restrict__ lds, DmaRows<kD
 // Token rows a tile row's items compute: the smallest of 32, 64, 128, 192 and 256 that holds its
 // routed rows.  Padding rows follow the routed ones when owner groups are not padded (a.compact),
 // so the rest of the tile row is nobody's output; with band padding in between, every row is taken.
-// Both launches decide alike, and the down launch reads only activation rows that were stored.
+// Gate/up stores the activation rows of that height and the down launch reads no others, but for
+// launches of explicit K parts (split_k over 1), which always take all 256: the rows past the height are
+// then an earlier run's, or were never written.  Each token row is a column of its own in the products,
+// so they reach padding outputs alone, which no epilogue stores.
 // The time of a height is its products from 128 rows up and its weight stream below, so the narrow
 // tiles end at 64.  Whole tile rows only, then these heights: 8 rows in each of 32 experts (H 7168,
 // F 2048) 700 -> 566 us, 16 in each of two (H 4096, F 14336) 231 -> 194, 256 on average in each of 64
@@ -511,8 +514,8 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
   auto quad_m = [&](int j) { return (kNarrow ? 0 : (wave >> 1) * (kRows / 2)) + j * 16 + lr; };
   // Operand rows: DMA instruction i of a wave fills weight-tile rows wave*64 + i*8 .. +7 and
   // token-tile rows (wave*kDmaX + i)*8 .. +7.  The bases are wave-uniform (scalar registers) and the
-  // offsets from them below 2^32: at most 256 rows of at most 2^17 bytes, or gathered token rows of
-  // a tensor below 4 GiB.
+  // offsets from them below 2^32: at most 256 rows of 2^17 bytes (hidden at most 2^16) or 2^20 (ffn
+  // below 2^19), or gathered token rows of a tensor below 4 GiB.
   DmaRows<kDmaPerThread> w;
   DmaRows<kDmaX> x;
   const uint32_t r8 = (uint32_t)lane >> 3;
@@ -606,9 +609,9 @@ __device__ __forceinline__ void producer_item(const ProducerArgs& a, uint32_t it
     const int c16 = tid & 15;
     const int f = col * kGuTileF + c16 * 8;
     uint16_t* blk = a.hws + ((size_t)(f / kTileK) * a.hws_rows) * kTileK + (f % kTileK);
-    // Padding rows are stored too: they gather a valid token row, so their activations are
-    // finite, and the down launch only uses them for padding outputs it never stores -- no
-    // per-row lookup sits between the staged tile and its stores.
+    // Padding rows up to the height are stored too: they gather a valid token row, and the down launch
+    // only uses them for padding outputs it never stores -- no per-row lookup sits between the staged
+    // tile and its stores.
     if (f < F) {
 #pragma unroll 4
       for (int p = 0; p < kRows / 16; ++p) {

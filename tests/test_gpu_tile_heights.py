@@ -52,3 +52,30 @@ def test_every_height_matches_the_oracle(n):
         for other in same[1:]:
             assert all(torch.equal(a, b) for a, b in zip(same[0], other)), f"split_k={k}"
     log(f"rows {n}: worst {worst:.2e}, rel {rel:.2e}")
+
+
+@pytest.mark.timeout(120)
+@pytest.mark.parametrize("split_k", [0, 2, 3, 4, 8])
+def test_an_earlier_call_s_activations_reach_no_output(split_k):
+    """Gate/up stores the activation rows of a tile row's height, a down launch of explicit K parts reads
+    all 256: the rest are an earlier call's, NaN here.  They are other token rows, so nothing that is
+    stored may see them."""
+    big = with_rows(257, 200)
+    for n in (1, 33, 65, 192):
+        wl = with_rows(n, 40)
+        ref = oracle_bufs(wl)
+        fresh = None
+        for poisoned in (False, True):
+            with B.MoeStage(wl.H, wl.F, wl.E_l, wl.R, wl.self_rank, big.rows, 0, 1, B.MOE_LOCAL_DIRECT, 0, split_k) as st:
+                if poisoned:
+                    dw = DeviceWorkload(torch, big)
+                    dw.x.fill_(0x7FC0)
+                    st.run_serial(*dw.args())
+                    assert all(np.all((b & 0x7F80) == 0x7F80) for b in dw.host_bufs() if b.size)
+                for overlapped in (False, True):
+                    dw = DeviceWorkload(torch, wl)
+                    (st.run if overlapped else st.run_serial)(*dw.args())
+                    st.query()
+                    compare(dw.host_bufs(), ref)
+                    fresh = dw.bufs if fresh is None else fresh
+                    assert all(torch.equal(a, b) for a, b in zip(fresh, dw.bufs)), (n, overlapped)
