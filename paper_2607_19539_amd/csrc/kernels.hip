@@ -56,7 +56,7 @@ constexpr int kRowsPerDma = 64 * 16 / kRowBytes;       // 8 rows per DMA instruc
 constexpr int kDmaPerThread = kTileM / kRowsPerDma / 4;  // 8 per weight block per thread
 // Epilogue staging: the finished tile goes through LDS (free once the pipeline drains) so
 // that global stores are whole 16-byte chunks of contiguous rows.  Rows are padded by 16
-// bytes so the 32 lanes writing one column of 32 rows hit distinct banks.
+// bytes, four banks of 64, so the 64 lanes that write 32 bytes of 16 rows load every bank alike.
 constexpr int kDownOutStride = kDownTileN * 2 + 16;    // 528 B per staged output row
 constexpr int kGuOutStride = kGuTileF * 2 + 16;        // 272 B per staged activation row
 // Words past both staging areas carry the next work item (its queue position, item word and
@@ -122,11 +122,6 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)LDS_PTR(p);
 }
 
-// 16 bytes per lane from global memory (scalar base + 32-bit lane offset) straight into
-// LDS at M0 + 16 * lane.  Issued as inline assembly so that the compiler's wait-count
-// pass does not serialise LDS reads behind every in-flight DMA: the pipeline waits for
-// exactly the stage it needs with an explicit vmcnt.  M0 is written right before the
-// load and is not used by any compiler-generated code in the producer.
 // 8 bytes stored as a relaxed agent-scope atomic store: it completes at the device's coherence
 // point, so once every wave's stores have completed (an explicit vmcnt(0) before a barrier)
 // another XCD can read the data after an agent-scope acquire, and the writer needs no L2
@@ -145,6 +140,11 @@ __device__ __forceinline__ uint64_t pack_f32x2(float lo, float hi) {
   return (uint64_t)__float_as_uint(lo) | ((uint64_t)__float_as_uint(hi) << 32);
 }
 
+// 16 bytes per lane from global memory (scalar base + 32-bit lane offset) straight into
+// LDS at M0 + 16 * lane.  Issued as inline assembly so that the compiler's wait-count
+// pass does not serialise LDS reads behind every in-flight DMA: the pipeline waits for
+// exactly the stage it needs with an explicit vmcnt.  M0 is written just before the
+// load and is not used by any compiler-generated code in the producer.
 // One wait state separates the scalar write of M0 from the load that reads it: a matrix
 // instruction where there is one (dma_m0 before it, dma16_at_m0 after), else an s_nop.
 template <int kLdsOff>
