@@ -189,10 +189,12 @@ typedef struct {
 typedef struct {
   int32_t runs;
   double stage_ms;     /* fork to join of each run (overlapped) or first to last kernel (serial) */
-  double producer_ms;  /* producer: gate/up launch start to down launch end              */
+  double producer_ms;  /* producer: gate/up launch start to down launch end, with the sums of
+                          split tail tiles except in serial runs (see scatter_ms)          */
   double gate_up_ms;   /* gate/up launch                                                 */
   double consumer_ms;  /* consumer kernel (overlapped runs)                              */
-  double scatter_ms;   /* scatter kernel (serial runs)                                   */
+  double scatter_ms;   /* scatter kernel (serial runs): the return copy and, with down_split_k
+                          0 and no MOE_DIRECT_ALL, the sums of the split tail tiles        */
   double plan_ms;      /* stage start until the plan is on the device and the counters are
                           reset: the upload of a host-built plan, or the device planner    */
 } moe_stage_times_t;

@@ -54,3 +54,24 @@ def test_stored_traffic_only_for_the_measured_source(bench, tmp_path, monkeypatc
     monkeypatch.setattr(bench, "TRAFFIC_FILE", str(tmp_path / "missing.md"))
     assert bench.stored_traffic() is None
 
+
+
+def test_no_share_of_peak_for_a_product_whose_sums_are_timed_elsewhere(bench):
+    """Serial runs with the default split add the tail tiles' parts in the scatter launch."""
+    class Wl:
+        H, F, rows = 4096, 14336, 8186
+
+        def flops(self):
+            return 6.0 * self.H * self.F * self.rows
+
+    r = {"ms": 2.2, "p10_ms": 2.2, "p50_ms": 2.2, "p90_ms": 2.2, "ms_with_kernel_events": 2.2, "warmup_runs": 1,
+         "gate_up_ms": 1.4, "producer_ms": 2.1, "scatter_ms": 0.04, "consumer_ms": 0.1,
+         "stats": {"gu_workgroups": 256, "down_workgroups": 256, "split_rows": 2, "copy_units": 4}}
+    assert bench.path_summary(Wl(), r, False, 0)["down_frac_of_peak"] == pytest.approx(
+        2.0 * 4096 * 14336 * 8186 / 0.7e-3 / 1e12 / bench.PEAK_BF16_TFLOPS)
+    serial = bench.path_summary(Wl(), r, True, 0)
+    assert serial["tail_sums_in"] == "scatter_us" and serial["scatter_us"] == pytest.approx(40)
+    assert not {"down_frac_of_peak", "producer_frac_of_peak"} & set(serial)
+    assert "down_frac_of_peak" in bench.path_summary(Wl(), r, True, 2)   # explicit parts: added in the launch
+    r["stats"]["split_rows"] = 0
+    assert "down_frac_of_peak" in bench.path_summary(Wl(), r, True, 0)   # nothing split
