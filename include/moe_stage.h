@@ -263,9 +263,9 @@ int moe_stage_run_serial(moe_stage_t h, const void* dispatched_x, const int32_t*
  * routing (moe_stage_plan_copy reads them back).
  *
  * The planner is chosen by the handle's capacity, since the routing is not known to the host: up to
- * max_rows 2048, 64 experts and 1024 (expert, rank) pairs one kernel resets the run and builds the
- * plan, above it five do, whatever the call's own rows (reset to plan ready, 110 rows in 2 experts: 18
- * and 30 us).  A program that decodes and prefills is quicker with a handle of its own for the decode
+ * max_rows 2048, 64 experts, 1024 (expert, rank) pairs and 8192 work items one kernel resets the run
+ * and builds the plan, above it five do, whatever the call's own rows (reset to plan ready, 110 rows in
+ * 2 experts: 18 and 30 us).  A program that decodes and prefills is quicker with a handle of its own for the decode
  * steps, sized for them.
  *
  * Precondition: the order a dispatch all-to-all delivers rows in -- within each expert, the
