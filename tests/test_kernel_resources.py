@@ -72,6 +72,54 @@ def test_consumer_fits_beside_a_producer_wave(kernels):
         assert int(f["agpr_count"]) == 256, name
 
 
+def _registers(text):
+    """Vector ('v'), accumulation ('a') and scalar ('s') registers that an instruction names."""
+    out = {(b, int(n)) for b, n in re.findall(r"\b([vas])(\d+)\b", text)}
+    for b, lo, hi in re.findall(r"\b([vas])\[(\d+):(\d+)\]", text):
+        out |= {(b, i) for i in range(int(lo), int(hi) + 1)}
+    return out
+
+
+def test_producer_assembly_keeps_its_distances(kernels):
+    """The matrix instructions and the LDS DMAs are assembly statements, which the compiler's own wait
+    states do not cover.  In the emitted order of each kernel: no vector instruction writes an operand
+    within two wait states before a matrix instruction reads it, none but a matrix instruction touches an
+    accumulator within 11 of its product, and no lane read writes a DMA's scalar base within 5."""
+    for name, f in by_name(kernels, "producer_kernel").items():
+        ins = [line.split(";")[0].strip() for line in f["body"].split("\n")
+               if line.startswith("\t") and not line.strip().startswith((".", ";"))]
+        states = [int(i.split()[1]) + 1 if i.startswith("s_nop") else 1 for i in ins]
+        n_mfma = 0
+
+        def before(i, limit):
+            ws = 0
+            while i > 0 and ws < limit:
+                i -= 1
+                yield ins[i]
+                ws += states[i]
+
+        for i, op in enumerate(ins):
+            if op.startswith("v_mfma"):
+                n_mfma += 1
+                reads = {r for r in _registers(op) if r[0] in "va"}
+                for p in before(i, 2):
+                    if p.startswith("v_") and not p.startswith(("v_mfma", "v_cmp")):
+                        assert not _registers(p.split(None, 1)[1].split(",")[0]) & reads, (name, p, op)
+                acc = {r for r in _registers(op) if r[0] == "a"}
+                ws = 0
+                for k in range(i + 1, len(ins)):
+                    if ws >= 11 or ins[k].startswith(("s_cbranch", "s_branch", "s_endpgm")):
+                        break
+                    assert ins[k].startswith("v_mfma") or not _registers(ins[k]) & acc, (name, op, ins[k])
+                    ws += 4 if ins[k].startswith("v_mfma") else states[k]
+            elif op.startswith("global_load_lds"):
+                base = {r for r in _registers(op) if r[0] == "s"}
+                for p in before(i, 5):
+                    if p.startswith(("v_readlane", "v_readfirstlane")):
+                        assert not _registers(p.split(None, 1)[1].split(",")[0]) & base, (name, p, op)
+        assert n_mfma > 100, name
+
+
 def test_every_split_variant_is_instantiated(kernels):
     names = set(by_name(kernels, "producer_kernel"))
     for down, split in ((0, 1), (1, 1), (1, 2), (1, 3), (1, 4), (1, 0), (1, "n1")):
