@@ -137,7 +137,7 @@ struct moe_stage_s {
   uint8_t* h_pinned = nullptr;               // one pinned allocation: both staging halves, the stamps
   uint8_t* h_stage[2] = {nullptr, nullptr};  // the staging halves, and as the device sees them:
   void* h_stage_dev[2] = {nullptr, nullptr};
-  hipEvent_t stage_free[2] = {nullptr, nullptr};
+  hipEvent_t stage_free[2] = {nullptr, nullptr};  // the last run that was staged in each half has ended
   int stage_idx = 0;
   uint32_t epoch = 0;
 
@@ -157,6 +157,8 @@ struct moe_stage_s {
   int cached_split = -1;
   hipStream_t s_cons = nullptr, s_prod = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join_c = nullptr, ev_join_p = nullptr, ev_done = nullptr;
+  hipEvent_t run_end = nullptr;   // what the run being enqueued records as its last packet
+  hipEvent_t last_done = nullptr; // and the last enqueued run recorded
   bool ran = false;
   bool counters_pending = false;  // the last run's device counters have not been read yet
   uint64_t last_span[2] = {0, 0};  // producer span of the last timestamped run
@@ -335,7 +337,7 @@ int prepare(moe_stage_s* h, bool overlapped, const void* x,
     queues[x] = P.gu_queue[x];
     queues[kXcds + 1 + x] = P.n_gu + P.down_queue[x];
   }
-  // Stage into pinned memory (wait until the copy that last used this half finished).
+  // Stage into pinned memory (wait until the run that last used this half has ended).
   const int si = h->stage_idx;
   h->stage_idx ^= 1;
   HIP_TRY(h, hipEventSynchronize(h->stage_free[si]));
@@ -363,7 +365,9 @@ int prepare(moe_stage_s* h, bool overlapped, const void* x,
   ia.up_dst = h->d_plan;
   ia.up_n16 = (int64_t)(lay->total / 16);  // every table starts and ends on 256 bytes
   HIP_TRY(h, launch_init(ia, stream));
-  HIP_TRY(h, hipEventRecord(h->stage_free[si], stream));
+  // The reset kernel has read the half by the time the run ends; an event right behind it would hold
+  // up the gate/up launch by 5.8 us, so the run's end frees the half, with the one event it records.
+  h->run_end = h->stage_free[si];
   h->epoch = epoch;
   h->last_lay = *lay;
   h->last_dev = false;
@@ -459,6 +463,7 @@ int prepare_device(moe_stage_s* h, bool overlapped, const void* x, const int32_t
   a.tail_rows = (int32_t*)(h->d_plan + lay->tail);
   a.ws = h->ws;
   HIP_TRY(h, launch_devplan(a, ia, h->max_items, h->num_cus, stream));
+  h->run_end = h->ev_done;
   h->epoch = epoch;
   h->last.plan_us =
       std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count();
@@ -827,12 +832,29 @@ int moe_stage_create(const moe_stage_config_t* cfg, moe_stage_t* out) {
   return MOE_OK;
 }
 
+// Records the run's last event, also where the run fails after its reset was enqueued: the reset
+// reads the staging half.  (The no-allocation entry point has no event.)
+struct RunEnd {
+  moe_stage_s* h;
+  hipStream_t stream;
+  RunEnd(moe_stage_s* h_, hipStream_t s) : h(h_), stream(s) { h->run_end = nullptr; }
+  hipError_t record() {
+    const hipEvent_t ev = h->run_end;
+    h->run_end = nullptr;
+    if (!ev) return hipSuccess;
+    h->last_done = ev;
+    return hipEventRecord(ev, stream);
+  }
+  ~RunEnd() { (void)record(); }
+};
+
 static int run_overlapped(moe_stage_t h, bool dev, const void* x, const int32_t* off,
                           const int32_t* src, const int32_t* slot, const void* w1, const void* w3,
                           const void* w2, void* const* ret, const int64_t* return_rows,
                           int32_t cu_split, void* stream_) {
   if (!h) return MOE_EINVAL;
   hipStream_t stream = (hipStream_t)stream_;
+  RunEnd end(h, stream);
   const bool autosplit = cu_split == 0;
   int auto_cand = -1, auto_slot = -1;
   if (autosplit) {
@@ -998,7 +1020,7 @@ static int run_overlapped(moe_stage_t h, bool dev, const void* x, const int32_t*
     HIP_TRY(h, hipEventRecord(tr->ev[5], stream));
     tr->kind = 0;
   }
-  HIP_TRY(h, hipEventRecord(h->ev_done, stream));
+  HIP_TRY(h, end.record());
   if (auto_slot >= 0) {
     HIP_TRY(h, launch_stamp(&h->autos.stamps[2 * auto_slot + 1], stream));
     HIP_TRY(h, hipEventRecord(h->autos.done[auto_slot], stream));
@@ -1017,6 +1039,7 @@ static int run_serial(moe_stage_t h, bool dev, const void* x, const int32_t* off
                       const void* w2, void* const* ret, const int64_t* return_rows, void* stream_) {
   if (!h) return MOE_EINVAL;
   hipStream_t stream = (hipStream_t)stream_;
+  RunEnd end(h, stream);
   const int pgrid = h->num_cus * h->producer_bpc;
   BlobLayout lay{};
   TimingRec* tr = timing_slot(h);
@@ -1068,7 +1091,7 @@ static int run_serial(moe_stage_t h, bool dev, const void* x, const int32_t* off
     HIP_TRY(h, hipEventRecord(tr->ev[5], stream));
     tr->kind = 1;
   }
-  if (h->ev_done) HIP_TRY(h, hipEventRecord(h->ev_done, stream));
+  HIP_TRY(h, end.record());
   h->ran = true;
   h->counters_pending = true;
   return MOE_OK;
@@ -1103,7 +1126,7 @@ int moe_stage_run_serial_devplan(moe_stage_t h, const void* x, const int32_t* of
 // Waits for the last run and reads its device counters once (the watchdog reports stay in
 // h->last until a query returns them).
 static int sync_counters(moe_stage_t h) {
-  if (h->ran) HIP_TRY(h, hipEventSynchronize(h->ev_done));
+  if (h->ran) HIP_TRY(h, hipEventSynchronize(h->last_done));
   if (h->counters_pending) {
     h->counters_pending = false;
     RunCounters c{};
@@ -1175,7 +1198,7 @@ int moe_stage_times(moe_stage_t h, int32_t reset, moe_stage_times_t* out) {
   if (!h || !out) return MOE_EINVAL;
   *out = moe_stage_times_t{};
   if (!(h->cfg.flags & MOE_KERNEL_TIMING)) return set_err(h, MOE_EINVAL, "MOE_KERNEL_TIMING not set");
-  if (h->ran) HIP_TRY(h, hipEventSynchronize(h->ev_done));
+  if (h->ran) HIP_TRY(h, hipEventSynchronize(h->last_done));
   for (int k = 0; k < h->ring_count; ++k) {
     TimingRec& r = h->ring[(h->ring_next - 1 - k + 2 * kTimingRing) % kTimingRing];
     float ms = 0;
@@ -1203,7 +1226,7 @@ int moe_stage_times(moe_stage_t h, int32_t reset, moe_stage_times_t* out) {
 // The last run's plan as the kernels saw it, read back from the device blob.
 static int read_header(moe_stage_t h, PlanHeader* hd) {
   if (!h->ran) return set_err(h, MOE_EINVAL, "no run yet");
-  HIP_TRY(h, hipEventSynchronize(h->ev_done));
+  HIP_TRY(h, hipEventSynchronize(h->last_done));
   HIP_TRY(h, hipMemcpy(hd, h->d_plan + h->last_lay.hdr, sizeof *hd, hipMemcpyDeviceToHost));
   return MOE_OK;
 }
